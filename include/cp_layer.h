@@ -60,19 +60,19 @@ int cpl_qkv_rope(const void* qkv, const void* q_norm_w, const void* k_norm_w,
 int cpl_swiglu(const void* gu, void* out, int32_t n_tokens, int32_t inter, void* stream);
 
 /* Projection: c[M][N] = a[M][K] . w[N][K]^T (+ r[M][N]), bf16 in and out, fp32
- * accumulation on the matrix cores (v_mfma_f32_32x32x16_bf16), for batches of
- * any size (the layer runs its QKV and output projections on it above the
- * skinny kernel's batch sizes).  M >= 1, N % 128 == 0, K % 32 == 0; a, w, c,
- * r and ws 16-byte aligned; r may be NULL or equal to c (in-place residual
- * add); a and w must not alias c.  Output tiles of 64-256 x 128-256 with K
- * staged through LDS; when the tiles alone would leave CUs idle, K is split
- * into slices whose fp32 partial tiles go to ws (the caller's device
- * memory, at least cpl_gemm_workspace_bytes(m, n, k) bytes to split fully;
- * with less, or ws NULL, the split shrinks or is skipped: same definition,
- * fewer workgroups).  The environment variables CPL_GEMM_CFG (tile
- * configuration 0-7: 64x128, 128x128, 128x256, 256x128 with 32 k per stage,
- * 64x128, 128x128 with 64, 256x256 with 32 and 64) and CPL_GEMM_SPLIT
- * (slices) override the choice. */
+ * accumulation on the matrix cores (v_mfma_f32_16x16x32_bf16), for batches of
+ * any size (the layer runs its projections on it above the skinny kernel's
+ * batch sizes).  M >= 1, N % 128 == 0, K % 32 == 0; a, w, c, r and ws 16-byte
+ * aligned; r may be NULL or equal to c (in-place residual add); a and w must
+ * not alias c.  Output tiles of 32-288 x 64-256 with K staged through LDS;
+ * when the tiles alone would leave CUs idle, K is split into up to 8 slices
+ * whose fp32 partial tiles go to ws (the caller's device memory, at least
+ * cpl_gemm_workspace_bytes(m, n, k) bytes for the split that suits the shape
+ * best; with less, or ws NULL, the split shrinks or is skipped: same
+ * definition, fewer workgroups).  Tile and split are chosen by estimated
+ * time; the environment variables CPL_GEMM_CFG (index into the kernel's table
+ * of tile configurations, where its columns divide N) and CPL_GEMM_SPLIT
+ * (slices, at most 8) override the choice. */
 int cpl_gemm(const void* a, const void* w, const void* r, void* c, int32_t m, int32_t n,
              int32_t k, void* ws, size_t ws_bytes, void* stream);
 

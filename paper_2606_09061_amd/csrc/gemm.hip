@@ -1,40 +1,42 @@
-// Tiled bf16 GEMM for the projections of the decoder layer around the
-// attention step (include/cp_layer.h, cpl_gemm):
+// bf16 GEMMs for the projections of the decoder layer around the attention
+// step (include/cp_layer.h, cpl_gemm):
 //     C[M][N] = A[M][K] . W[N][K]^T (+ R[M][N]),   fp32 accumulation, bf16 out.
-// Both operands are K-contiguous rows, which is exactly how the matrix cores
-// take their operands: with v_mfma_f32_32x32x16_bf16 every lane holds 16
-// bytes (8 consecutive k) of one row of each operand.
+// Both operands are K-contiguous rows, which is how the matrix cores take
+// them: with v_mfma_f32_16x16x32_bf16 lane l holds 16 bytes (8 consecutive k)
+// of row l % 16.  The products are formed transposed, D^T (16 n x 16 m) =
+// W_blk . A_blk^T, so a lane's accumulators hold 4 consecutive n of one m.
 //
-// A workgroup of 4 (2 x 2) or 8 (2 x 4) waves computes a BM x BN tile of C,
-// each wave a (BM/2) x (BN/2 or BN/4) part of it as blocks of 32 x 32.  The
-// products are formed transposed, D^T (32 n x 32 m) = W_blk . A_blk^T, so a
-// lane's accumulators hold 4 consecutive n of one m: the epilogue writes 8
-// contiguous bytes per lane and row.
+// A workgroup of 8 waves (WM x WN) computes a BM x BN tile of C.  K is walked
+// in stages of 64 (128-byte row pieces, whole cache lines), copied straight
+// from global memory into a ring of NS LDS slots (global_load_lds_dwordx4, no
+// register staging).  The copies are written as the instruction itself: the
+// compiler does not track them, and the explicit vmcnt waits are the only
+// ones.  A row's 16-byte chunk c is stored at chunk c ^ ((row >> 1) & 7), so
+// the 16 lanes of a phase of an operand read hit 16 distinct bank groups.
 //
-// K is walked in stages of BK.  A stage's A and W tiles are copied from
-// global memory straight into LDS (global_load_lds_dwordx4: 16 bytes per
-// lane, no register staging) into a ring of STAGES buffers, issued
-// STAGES - 1 stages ahead of their use; one barrier per stage, after an
-// explicit wait for exactly that stage's copies.  A tile row holds BK / 8
-// chunks of 16 bytes; chunk c of row r is stored at chunk c ^ swz(r), so the
-// 16 lanes of every phase of an operand read (rows r..r+15, one logical
-// chunk) hit 16 distinct 16-byte bank groups.
+// Two kernels share that layout and differ in how a stage is worked off:
 //
-// Split over K: with a workspace, a grid too small to fill the GPU is
-// multiplied by S slices of K; slice s writes its fp32 partial tile to
-// ws[s][M][N] and a second kernel adds the S partials (and R) and rounds.
+// * gemm_tile_kernel, for tiles whose MFMAs take longer than their copies
+//   (large batches).  Two waves share a SIMD; waves 0-3 and 4-7 run half a
+//   stage out of step, so that while one reads operands from LDS the other
+//   keeps the matrix pipe busy.
+// * gemm_stream_kernel, for the short tiles of decode-sized batches, which
+//   are bound by the weight stream: one barrier per stage, the next stage's
+//   operands read while the current one is multiplied.
 //
-// Workgroup order: workgroup g runs on XCD g mod 8; each XCD takes whole
-// column blocks of W and walks them in row groups of up to 8 row blocks, so
-// that the workgroups resident on an XCD share both A and W panels in its
-// L2 (with row blocks innermost across all of M, a 4096-row A would stream
-// from the last-level cache once per pair of column blocks).
+// Split over K: a grid too small to fill the GPU is multiplied by S slices of
+// K; slice s writes its fp32 partial tile to ws[s][M][N] and a second kernel
+// adds the S partials (and R) and rounds.
+//
+// Workgroup order: workgroup g runs on XCD g mod 8, and each XCD takes a
+// contiguous run of tiles, ordered in groups of 4 row blocks with the row
+// block fastest, so that the ~32 tiles resident on an XCD share their A and W
+// panels in its L2.
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 #include <stdlib.h>
-
-#include <type_traits>
 
 #include "cp_layer.h"
 
@@ -42,21 +44,33 @@ namespace {
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kXcds = 8;
-constexpr int kMinSliceK = 256;  // shortest K slice of a split
+constexpr int kCus = 256;
+constexpr int kRowGroup = 4;             // row blocks per group of the tile order
+constexpr int kStageK = 64;              // k per stage
+constexpr int kRow = kStageK * 2;        // bytes of a staged row
+constexpr int kMaxLds = 160 * 1024;
+constexpr int kMaxSplit = 8;
 
-__device__ __forceinline__ f32x16_t mfma(uint4 a, uint4 b, f32x16_t c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a),
+__device__ __forceinline__ f32x4_t mfma(uint4 a, uint4 b, f32x4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
                                                  __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
 }
 
-// 16 bytes per lane from global memory into LDS at lds + 16 * lane
-// (`lds` wave-uniform).  The address-space cast exists only in the device pass.
-__device__ __forceinline__ void copy16_to_lds(const void* src, uint8_t* lds) {
+// 16 bytes per lane from base + off into LDS at dst + 16 * lane (base and dst
+// wave-uniform).  `stream`: non-temporal, for weights that one workgroup
+// reads.  (The register constraints exist only in the device pass.)
+__device__ __forceinline__ void copy16_to_lds(const char* base, uint32_t off, uint32_t dst,
+                                              bool stream) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  __builtin_amdgcn_global_load_lds(src, (lds_ptr_t)lds, 16, 0, 0);
+  if (stream)
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(off), "s"(base), "{m0}"(dst)
+                 : "memory");
+  else
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(dst)
+                 : "memory");
 #endif
 }
 
@@ -66,32 +80,31 @@ __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt");
   __builtin_amdgcn_s_waitcnt((N & 15) | (0x7 << 4) | (0xF << 8) | ((N >> 4) << 14));
 }
+// s_waitcnt lgkmcnt(0): this wave's LDS reads have returned
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F); }
 
-// waits until at most `later` stages' copies (LOADS each) are pending
-template <int LOADS, int MAXLATER>
+// waits until at most `later` (<= MAX) stages' copies, L each, are pending
+template <int L, int MAX>
 __device__ __forceinline__ void wait_stages(int later) {
-  if constexpr (MAXLATER >= 3) {
-    if (later >= 3) { wait_vmcnt<3 * LOADS>(); return; }
-  }
-  if constexpr (MAXLATER >= 2) {
-    if (later >= 2) { wait_vmcnt<2 * LOADS>(); return; }
-  }
-  if (later >= 1) { wait_vmcnt<LOADS>(); return; }
-  wait_vmcnt<0>();
-}
-
-// Compile-time loop: f(std::integral_constant<int, I>) for I in [I0, N).
-template <int I0, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I0 < N) {
-    f(std::integral_constant<int, I0>());
-    static_for<I0 + 1, N>(f);
+  if constexpr (MAX > 0) {
+    if (later >= MAX) {
+      wait_vmcnt<MAX * L>();
+      return;
+    }
+    wait_stages<L, MAX - 1>(later);
+  } else {
+    wait_vmcnt<0>();
   }
 }
 
 // Workgroup barrier without the memory fence of __syncthreads, which would
-// also wait for the copies of later stages (the waits above are explicit).
-__device__ __forceinline__ void barrier() { asm volatile("s_barrier" ::: "memory"); }
+// also wait for the copies of later stages (the waits above are explicit);
+// nothing is moved across it.
+__device__ __forceinline__ void barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
 
 __device__ __forceinline__ uint16_t to_bf16(float a) {
   return __builtin_bit_cast(uint16_t, (__bf16)a);  // nearest even
@@ -102,274 +115,540 @@ __device__ __forceinline__ uint32_t pack(float a, float b) {
 __device__ __forceinline__ float lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-template <int BM, int BN, int BK, int STAGES, int WGM = 2, int WGN = 2>
-struct GemmGeom {
-  static constexpr int NW = WGM * WGN;               // waves
-  static constexpr int WTM = BM / WGM, WTN = BN / WGN;  // wave tile
-  static constexpr int TM = WTM / 32, TN = WTN / 32;    // 32 x 32 blocks per wave
-  static constexpr int ROW = BK * 2;                 // bytes per tile row
-  static constexpr int CPR = ROW / 16;               // 16-byte chunks per row
-  static constexpr int RPP = 1024 / ROW;             // rows per 1 KiB copy
-  static constexpr int KS = BK / 16;                 // MFMA k-steps per stage
-  static constexpr int A_BYTES = BM * ROW, W_BYTES = BN * ROW;
-  static constexpr int STAGE_BYTES = A_BYTES + W_BYTES;
-  static constexpr int A_PW = A_BYTES / 1024 / NW, W_PW = W_BYTES / 1024 / NW;  // copies per wave
-  static constexpr int LOADS = A_PW + W_PW;
-  static_assert(BK == 32 || BK == 64, "BK");
-  static_assert(A_PW * 1024 * NW == A_BYTES && W_PW * 1024 * NW == W_BYTES, "copies per wave");
-  static_assert(LOADS * (STAGES - 1) < 64 && STAGES <= 4, "vmcnt range");
-  // stored chunk of logical chunk c in row r: 16 consecutive rows (one
-  // 16-lane phase of an operand read) land in 16 distinct 16-byte groups of
-  // the 256-byte bank width
-  __device__ static int swz(int r, int c) {
-    return CPR == 8 ? c ^ ((r >> 1) & 7) : c ^ ((r >> 2) & 3);
-  }
+struct GemmArgs {
+  const uint16_t* a;
+  const uint16_t* w;
+  const uint16_t* r;   // residual or NULL
+  uint16_t* c;
+  float* part;         // split partials, or NULL: C is written directly
+  int m, n, k;
+  int split;
+  bool stream_w;       // copy W non-temporally
 };
 
-template <int BM, int BN, int BK, int STAGES, int WGM, int WGN>
-__global__ __launch_bounds__(64 * WGM * WGN, 8 / (WGM * WGN)) void gemm_kernel(
-    const uint16_t* __restrict__ A, const uint16_t* __restrict__ W, const uint16_t* R,
-    uint16_t* C, float* __restrict__ part, int M, int N, int K, int S) {
-  using G = GemmGeom<BM, BN, BK, STAGES, WGM, WGN>;
-  constexpr int TM = G::TM, TN = G::TN, ROW = G::ROW;
-  // one array per ring buffer, every access naming its array at compile
-  // time: the compiler then tells the copies in flight into one buffer from
-  // the operand reads of another, and waits only where they meet
-  constexpr int SB = G::STAGE_BYTES;
-  __shared__ __attribute__((aligned(1024))) uint8_t sb0[SB];
-  __shared__ __attribute__((aligned(1024))) uint8_t sb1[SB];
-  __shared__ __attribute__((aligned(1024))) uint8_t sb2[STAGES > 2 ? SB : 1024];
-  __shared__ __attribute__((aligned(1024))) uint8_t sb3[STAGES > 3 ? SB : 1024];
-  auto buf = [&](auto i_c) -> uint8_t* {
-    constexpr int i = decltype(i_c)::value % STAGES;
-    if constexpr (i == 0) return sb0;
-    else if constexpr (i == 1) return sb1;
-    else if constexpr (i == 2) return sb2;
-    else return sb3;
+// The tile and K slice of a workgroup.
+struct Tile {
+  int m0, n0;    // first row and column
+  int slice;
+  int st0, nk;   // first stage and stages
+};
+
+// false: no tile for this workgroup (the grid is rounded up to the XCDs)
+template <int BM, int BN>
+__device__ __forceinline__ bool pick_tile(const GemmArgs& g, Tile& t) {
+  const int mb = (g.m + BM - 1) / BM, nb = g.n / BN, tiles = mb * nb * g.split;
+  const int per = (tiles + kXcds - 1) / kXcds;
+  int i = (int)(blockIdx.x % kXcds) * per + (int)(blockIdx.x / kXcds);
+  if (i >= tiles || (int)(blockIdx.x / kXcds) >= per) return false;
+  t.slice = i / (mb * nb);
+  i -= t.slice * mb * nb;
+  const int group = i / (kRowGroup * nb);
+  i -= group * kRowGroup * nb;
+  const int rows = min(kRowGroup, mb - group * kRowGroup);
+  t.n0 = i / rows * BN;
+  t.m0 = (group * kRowGroup + i % rows) * BM;
+  const int stages = (g.k + kStageK - 1) / kStageK;
+  t.st0 = (int)((int64_t)t.slice * stages / g.split);
+  t.nk = (int)((int64_t)(t.slice + 1) * stages / g.split) - t.st0;
+  return true;
+}
+
+// One 1 KiB piece of a staged tile: 8 rows of `src` [limit][K] from `row` (rows past the
+// last read the last: their products are discarded).
+struct Piece {
+  const char* base;  // wave-uniform
+  uint32_t off;      // this lane's byte offset from it (7 rows of K at most)
+  uint32_t dst;      // LDS address in slot 0
+};
+__device__ __forceinline__ Piece piece(const uint16_t* src, int k, int row0, int limit, int row,
+                                       int st0, uint32_t lds, int lane) {
+  const int rr = row + (lane >> 3);
+  const int first = min(row0 + row, limit - 1);
+  const int chunk = (lane & 7) ^ ((rr >> 1) & 7);
+  Piece p;
+  p.base = reinterpret_cast<const char*>(src + (int64_t)first * k + (int64_t)st0 * kStageK);
+  p.off = (uint32_t)(min(row0 + rr, limit - 1) - first) * (uint32_t)k * 2 + (uint32_t)chunk * 16;
+  p.dst = lds + row * kRow;
+  return p;
+}
+
+// Byte offset inside a 16-row operand block of lane l's chunk, k-half h of a
+// stage (row l % 16, logical chunk 4 h + l / 16).
+__device__ __forceinline__ uint32_t operand_offset(int h, int lane) {
+  const int r = lane & 15;
+  return (uint32_t)(r * kRow + (((4 * h + (lane >> 4)) ^ ((r >> 1) & 7)) * 16));
+}
+__device__ __forceinline__ uint4 lds16(const uint8_t* p) { return *reinterpret_cast<const uint4*>(p); }
+
+// acc[i][j] register e holds m = m1 + 16 i + lane % 16, n = n1 + 16 j + 4 (lane / 16) + e.
+// Partials go out as they are (16 bytes per lane).  bf16 rows pass through a
+// wave-private LDS slice, so that they leave in 16-byte pieces, consecutive
+// lanes along a row; every wave is past its last operand read (a barrier
+// before the call).
+template <int TM, int TN>
+__device__ __forceinline__ void store_tile(const GemmArgs& g, int slice, int m1, int n1,
+                                           f32x4_t (&acc)[TM][TN], uint8_t* lds, int lane) {
+  if (g.part) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int m = m1 + 16 * i + (lane & 15);
+      if (m >= g.m) continue;
+      float* row = g.part + ((int64_t)slice * g.m + m) * g.n + n1 + 4 * (lane >> 4);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) *reinterpret_cast<f32x4_t*>(row + 16 * j) = acc[i][j];
+    }
+    return;
+  }
+  constexpr int PITCH = TN * 32 + 16;  // bytes of a staged row
+  constexpr int CH = TN * 2;           // its 16-byte chunks
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+      *reinterpret_cast<uint2*>(lds + (lane & 15) * PITCH + j * 32 + (lane >> 4) * 8) =
+          make_uint2(pack(acc[i][j][0], acc[i][j][1]), pack(acc[i][j][2], acc[i][j][3]));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int x0 = 0; x0 < 16 * CH; x0 += 64) {
+      const int x = x0 + lane;
+      const int m = m1 + 16 * i + x / CH;
+      if (x < 16 * CH && m < g.m)
+        *reinterpret_cast<uint4*>(g.c + (int64_t)m * g.n + n1 + (x % CH) * 8) =
+            lds16(lds + (x / CH) * PITCH + (x % CH) * 16);
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Adds the residual in place of the accumulators' layout (8 bytes per lane and block).
+template <int TM, int TN>
+__device__ __forceinline__ void add_residual(const GemmArgs& g, int m1, int n1,
+                                             f32x4_t (&acc)[TM][TN], int lane) {
+  if (g.part || !g.r) return;
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int m = m1 + 16 * i + (lane & 15);
+    if (m >= g.m) continue;
+    const uint16_t* row = g.r + (int64_t)m * g.n + n1 + 4 * (lane >> 4);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const uint2 r = *reinterpret_cast<const uint2*>(row + 16 * j);
+      acc[i][j][0] += lo(r.x), acc[i][j][1] += hi(r.x);
+      acc[i][j][2] += lo(r.y), acc[i][j][3] += hi(r.y);
+    }
+  }
+}
+
+// Large tiles.  The row blocks of a wave are worked off in two parts, the
+// first T0 and the other T1, each as a read phase (operands from LDS to
+// registers) and an MFMA phase; W's operands stay in registers over both.
+// Waves 0-3 start one phase ahead of waves 4-7 (the latter pass one more
+// barrier first), and SIMD s holds waves s and s + 4, so in every phase one
+// of them reads while the other multiplies.  With phases 4k.. for stage k of
+// the first group:
+//     first group   read 0 | mfma 0 | read 1 | mfma 1
+//     second group  mfma 1 of stage k-1 | read 0 | mfma 0 | read 1
+// Slot k % NS is refilled as soon as both groups have read it: its W rows in
+// read 1 of stage k (W of stage k + NS), its A rows in read 0 of stage k + 1.
+// A group copies only the A rows that it reads itself, so each copy has about
+// four to six phases (2-3k cycles at 256 x 256) to land with two slots.
+//
+// A 256 x 256 x 64 stage takes 2,048 matrix-pipe cycles per SIMD, 64 KiB of
+// copies and 192 KiB of operand reads per CU.  Measured against the earlier
+// 128 x 128 tiles (one barrier and one wait per stage, two workgroups per
+// CU): 2048 x 6144 x 4096 142 -> 84 us (1.23 PFLOP/s), 4096 x 24576 x 4096
+// 847 -> 594 us (1.39 PFLOP/s; a loop of these MFMAs and barriers without
+// copies or reads takes 458 us at the clock that the power limit leaves).
+// Tried and left out: a single wait and K-half phases (640 us), deeper rings
+// of 32-k stages (664), prefetching lines to L2 (+10 %), s_setprio around
+// the MFMAs (+1-3 %), other pairings of the groups (750).
+template <int WM, int WN, int TM, int TN, int NS>
+__global__ __launch_bounds__(512, 2) void gemm_tile_kernel(GemmArgs g) {
+  constexpr int BM = WM * TM * 16, BN = WN * TN * 16, SB = (BM + BN) * kRow;
+  constexpr int T0 = TM / 2, T1 = TM - T0;
+  constexpr int GP = BM / 16, GP0 = (WM / 2) * T0 * 2;  // a group's A pieces, those of the T0 parts
+  constexpr int NA = (GP + 3) / 4, NA0 = (GP0 + 3) / 4; // per wave
+  constexpr int PW = BN / 8, NW = (PW + 7) / 8;
+  constexpr int L = NA + NW;
+  static_assert(WM * WN == 8 && WM % 2 == 0 && T0 > 0, "waves");
+  static_assert(SB * NS <= kMaxLds && (NS - 1) * L < 64, "ring");
+  static_assert(8 * 16 * (TN * 32 + 16) <= SB * NS, "store slices");
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[SB * NS];
+  Tile t;
+  if (!pick_tile<BM, BN>(g, t)) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN, group = wave >> 2;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
+  const bool stream = g.stream_w;
+  const int nk = t.nk;
+
+  // the group's A pieces, the T0 parts first, dealt in turn to its 4 waves;
+  // W's to all 8 (where they do not divide, the last piece is copied twice)
+  Piece pa[NA], pw[NW];
+#pragma unroll
+  for (int j = 0; j < NA; ++j) {
+    const int x = min(j * 4 + (wave & 3), GP - 1);
+    const bool first = x < GP0;
+    const int y = first ? x : x - GP0, per = (first ? T0 : T1) * 2;
+    const int row = group * (BM / 2) + (y / per) * TM * 16 + (first ? 0 : T0 * 16) + (y % per) * 8;
+    pa[j] = piece(g.a, g.k, t.m0, g.m, row, t.st0, lds0, lane);
+  }
+#pragma unroll
+  for (int j = 0; j < NW; ++j)
+    pw[j] = piece(g.w, g.k, t.n0, g.n, min(j * 8 + wave, PW - 1) * 8, t.st0, lds0 + BM * kRow, lane);
+  auto issue_a = [&](int st, int slot) {
+#pragma unroll
+    for (int j = 0; j < NA; ++j)
+      copy16_to_lds(pa[j].base + (int64_t)st * kRow, pa[j].off, pa[j].dst + slot * SB, false);
+  };
+  auto issue_w = [&](int st, int slot) {
+#pragma unroll
+    for (int j = 0; j < NW; ++j)
+      copy16_to_lds(pw[j].base + (int64_t)st * kRow, pw[j].off, pw[j].dst + slot * SB, stream);
   };
 
-  // ---- tile and K slice of this workgroup.  XCD x = g mod 8 owns column
-  // blocks x, x + 8, ...; its workgroups run row groups of GM row blocks
-  // against all its column blocks in turn (row block fastest), so the
-  // workgroups resident on an XCD at once share GM row panels of A and a
-  // few column panels of W in its L2
-  const int MB = (M + BM - 1) / BM, NB = N / BN;
-  const int NBX = (NB + kXcds - 1) / kXcds;
-  const int GM = MB % 8 == 0 ? 8 : MB % 4 == 0 ? 4 : MB;
-  const int g = blockIdx.x;
-  int t = g / kXcds;
-  const int m_in = t % GM;
-  t /= GM;
-  const int sl = t % S;
-  t /= S;
-  const int nb = (t % NBX) * kXcds + g % kXcds;
-  const int mb = (t / NBX) * GM + m_in;
-  if (nb >= NB) return;
-  const int m0 = mb * BM, n0 = nb * BN;
-  const int kslice = K / S;  // a multiple of BK
-  const int kbeg = sl * kslice;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WGN, wn = wave % WGN;
-
-  // ---- copy geometry: piece p of a tile = rows [RPP p, RPP (p + 1)); lane l
-  // writes row RPP p + l / CPR at stored chunk l % CPR
-  const int crow = lane / G::CPR;
-  const uint16_t* a_src[G::A_PW];
-  const uint16_t* w_src[G::W_PW];
-#pragma unroll
-  for (int i = 0; i < G::A_PW; ++i) {
-    const int r = (wave * G::A_PW + i) * G::RPP + crow;
-    const int c = G::swz(r, lane % G::CPR);  // the swizzle is an involution
-    const int m = min(m0 + r, M - 1);        // rows past M read row M-1 (results discarded)
-    a_src[i] = A + (int64_t)m * K + kbeg + c * 8;
-  }
-#pragma unroll
-  for (int i = 0; i < G::W_PW; ++i) {
-    const int r = (wave * G::W_PW + i) * G::RPP + crow;
-    const int c = G::swz(r, lane % G::CPR);
-    w_src[i] = W + (int64_t)(n0 + r) * K + kbeg + c * 8;
-  }
-  auto issue = [&](int st, uint8_t* base) {
-    const int k0 = st * BK;
-#pragma unroll
-    for (int i = 0; i < G::A_PW; ++i)
-      copy16_to_lds(a_src[i] + k0, base + (wave * G::A_PW + i) * 1024);
-#pragma unroll
-    for (int i = 0; i < G::W_PW; ++i)
-      copy16_to_lds(w_src[i] + k0, base + G::A_BYTES + (wave * G::W_PW + i) * 1024);
-  };
-
-  // ---- operand reads: k-step ks of a stage, 32-row block: lane l reads
-  // row l % 32 of the block, logical chunk 2 ks + l / 32 (block offsets are
-  // multiples of 32 rows, which leave the swizzle unchanged)
-  uint32_t ofs[G::KS];
-#pragma unroll
-  for (int ks = 0; ks < G::KS; ++ks) {
-    const int r = lane & 31;
-    ofs[ks] = (uint32_t)(r * ROW + G::swz(r, 2 * ks + (lane >> 5)) * 16);
-  }
-
-  f32x16_t acc[TM][TN];
+  const uint32_t ofs[2] = {operand_offset(0, lane), operand_offset(1, lane)};
+  const uint8_t* a_lds = smem + wm * TM * 16 * kRow;
+  const uint8_t* w_lds = smem + (BM + wn * TN * 16) * kRow;
+  f32x4_t acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int jn = 0; jn < TN; ++jn)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][jn][r] = 0.f;
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
-  const int nk = kslice / BK;
-  static_for<0, STAGES - 1>([&](auto s_c) {
-    if (decltype(s_c)::value < nk) issue(decltype(s_c)::value, buf(s_c));
-  });
-
-  // stages in groups of GROUP (a multiple of STAGES), so that every buffer
-  // index is a constant; the compiler drains the copies once per group (at
-  // the loop head it no longer knows which buffer each pending copy fills)
-  constexpr int GROUP = STAGES * (8 / STAGES);
-  for (int kb0 = 0; kb0 < nk; kb0 += GROUP) {
-    static_for<0, GROUP>([&](auto i_c) {
-      constexpr int i = decltype(i_c)::value;
-      const int kb = kb0 + i;
-      if (kb >= nk) return;
-      // stage kb has landed once at most the later stages' copies are pending
-      wait_stages<G::LOADS, STAGES - 2>(min(STAGES - 2, nk - 1 - kb));
-      barrier();  // every wave's copies of stage kb are in; stage kb-1's buffer is free
-      if (kb + STAGES - 1 < nk)
-        issue(kb + STAGES - 1, buf(std::integral_constant<int, i + STAGES - 1>()));
-      const uint8_t* base = buf(i_c);
-      const uint8_t* as = base + wm * G::WTM * ROW;
-      const uint8_t* ws = base + G::A_BYTES + wn * G::WTN * ROW;
+  // copies are issued in the order W0 A0 W1 A1 ..., here up to W of stage
+  // NS - 1; each wait below allows those issued after what it waits for, and
+  // near the end, where fewer follow, waits for all
 #pragma unroll
-      for (int ks = 0; ks < G::KS; ++ks) {
-        uint4 av[TM], wv[TN];
+  for (int s = 0; s < NS; ++s)
+    if (s < nk) {
+      issue_w(s, s);
+      if (s < NS - 1) issue_a(s, s);
+    }
+  if (nk >= NS)
+    wait_vmcnt<(NS - 1) * L - NA>();
+  else
+    wait_vmcnt<0>();
+  barrier();
+  if (group) barrier();
+  int slot = 0;
+  for (int k = 0; k < nk; ++k) {
+    const uint8_t* as = a_lds + slot * SB;
+    const uint8_t* ws = w_lds + slot * SB;
+    uint4 wv[2][TN], av[2][T1];
+    // read 0
 #pragma unroll
-        for (int ii = 0; ii < TM; ++ii)
-          av[ii] = *reinterpret_cast<const uint4*>(as + ii * 32 * ROW + ofs[ks]);
+    for (int h = 0; h < 2; ++h) {
 #pragma unroll
-        for (int jn = 0; jn < TN; ++jn)
-          wv[jn] = *reinterpret_cast<const uint4*>(ws + jn * 32 * ROW + ofs[ks]);
+      for (int j = 0; j < TN; ++j) wv[h][j] = lds16(ws + ofs[h] + j * 16 * kRow);
 #pragma unroll
-        for (int ii = 0; ii < TM; ++ii)
+      for (int i = 0; i < T0; ++i) av[h][i] = lds16(as + ofs[h] + i * 16 * kRow);
+    }
+    const bool more_a = k + NS - 1 < nk, more_w = k + NS < nk;
+    if (more_a) issue_a(k + NS - 1, slot == 0 ? NS - 1 : slot - 1);
+    wait_lds();
+    barrier();
+    // mfma 0
 #pragma unroll
-          for (int jn = 0; jn < TN; ++jn) acc[ii][jn] = mfma(wv[jn], av[ii], acc[ii][jn]);
-      }
-    });
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < T0; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = mfma(wv[h][j], av[h][i], acc[i][j]);
+    if (more_a)  // this stage's other A rows
+      wait_vmcnt<(NS - 1) * L>();
+    else
+      wait_vmcnt<0>();
+    barrier();
+    // read 1
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < T1; ++i) av[h][i] = lds16(as + ofs[h] + (T0 + i) * 16 * kRow);
+    if (more_w) issue_w(k + NS, slot);
+    wait_lds();
+    if (more_w)  // the next stage's W
+      wait_vmcnt<(NS - 1) * L>();
+    else
+      wait_vmcnt<0>();
+    barrier();
+    // mfma 1
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < T1; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[T0 + i][j] = mfma(wv[h][j], av[h][i], acc[T0 + i][j]);
+    if (more_w) wait_vmcnt<(NS - 1) * L - NA0>();  // the next stage's first A rows
+    barrier();
+    slot = slot + 1 == NS ? 0 : slot + 1;
   }
-
-  // ---- epilogue: acc[i][jn] register 4q + e holds
-  //   m = m0 + wm*WTM + 32i + lane%32,   n = n0 + wn*WTN + 32jn + 8q + 4(lane/32) + e
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int m = m0 + wm * G::WTM + 32 * i + (lane & 31);
-    if (m >= M) continue;
-#pragma unroll
-    for (int jn = 0; jn < TN; ++jn)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int n = n0 + wn * G::WTN + 32 * jn + 8 * q + 4 * (lane >> 5);
-        const int64_t off = (int64_t)m * N + n;
-        float v0 = acc[i][jn][4 * q], v1 = acc[i][jn][4 * q + 1];
-        float v2 = acc[i][jn][4 * q + 2], v3 = acc[i][jn][4 * q + 3];
-        if (part) {  // fp32 partial of slice sl
-          *reinterpret_cast<float4*>(part + (int64_t)sl * M * N + off) =
-              make_float4(v0, v1, v2, v3);
-          continue;
-        }
-        if (R) {
-          const uint2 r = *reinterpret_cast<const uint2*>(R + off);
-          v0 += lo(r.x), v1 += hi(r.x), v2 += lo(r.y), v3 += hi(r.y);
-        }
-        *reinterpret_cast<uint2*>(C + off) = make_uint2(pack(v0, v1), pack(v2, v3));
-      }
-  }
+  if (!group) barrier();
+  const int m1 = t.m0 + wm * TM * 16, n1 = t.n0 + wn * TN * 16;
+  add_residual<TM, TN>(g, m1, n1, acc, lane);
+  store_tile<TM, TN>(g, t.slice, m1, n1, acc, smem + wave * 16 * (TN * 32 + 16), lane);
 }
 
-// C = sum over S slices of part (+ R), 4 elements per thread
+// Short tiles.  One barrier per stage: behind it a wave issues the copies of
+// stage k + NS into the slot that every wave has just finished reading, the
+// LDS reads of stage k + 1, and the MFMAs of stage k from registers.  HALF:
+// K is an odd number of 32s, and the last stage's second half is left out
+// (its copies re-read the first half, so nothing past a row is touched).
+//
+// Bound by the weight stream: with W's copies non-temporal and the ring
+// holding 16-48 KiB of W in flight per CU, 24 rows x 24576 x 4096 take 37.7
+// us (5.3 TB/s; 42.7 with ordinary copies), 24 x 4096 x 12288 20.5 us.
+template <int WM, int WN, int TM, int TN, int NS, bool HALF = false>
+__global__ __launch_bounds__(512, 2) void gemm_stream_kernel(GemmArgs g) {
+  constexpr int BM = WM * TM * 16, BN = WN * TN * 16, SB = (BM + BN) * kRow;
+  constexpr int PA = BM / 8, PW = BN / 8, NA = (PA + 7) / 8, NW = (PW + 7) / 8, L = NA + NW;
+  static_assert(WM * WN == 8 && SB * NS <= kMaxLds && (NS - 1) * L < 64, "ring");
+  static_assert(8 * 16 * (TN * 32 + 16) <= SB * NS, "store slices");
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[SB * NS];
+  Tile t;
+  if (!pick_tile<BM, BN>(g, t)) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
+  const bool stream = g.stream_w;
+  const int nk = t.nk;
+  // the slice's last stage when it holds only 32 k, else past the end
+  const int half = HALF && t.st0 + nk == (g.k + kStageK - 1) / kStageK ? nk - 1 : nk;
+
+  Piece pa[NA], pw[NW];
+#pragma unroll
+  for (int j = 0; j < NA; ++j)
+    pa[j] = piece(g.a, g.k, t.m0, g.m, min(j * 8 + wave, PA - 1) * 8, t.st0, lds0, lane);
+#pragma unroll
+  for (int j = 0; j < NW; ++j)
+    pw[j] = piece(g.w, g.k, t.n0, g.n, min(j * 8 + wave, PW - 1) * 8, t.st0, lds0 + BM * kRow, lane);
+  auto issue = [&](int st, int slot) {
+    // chunks 4-7 of a half stage read chunks 0-3 (a K row's chunk offset is
+    // below 128 bytes, and K a multiple of 64 bytes: bit 6 is the half)
+    auto cut = [&](uint32_t off, int row_chunk) {
+      return HALF && st == half && row_chunk >= 4 ? off - 64 : off;
+    };
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+      const int row = min(j * 8 + wave, PW - 1) * 8 + (lane >> 3);
+      copy16_to_lds(pw[j].base + (int64_t)st * kRow, cut(pw[j].off, (lane & 7) ^ ((row >> 1) & 7)),
+                    pw[j].dst + slot * SB, stream);
+    }
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {
+      const int row = min(j * 8 + wave, PA - 1) * 8 + (lane >> 3);
+      copy16_to_lds(pa[j].base + (int64_t)st * kRow, cut(pa[j].off, (lane & 7) ^ ((row >> 1) & 7)),
+                    pa[j].dst + slot * SB, false);
+    }
+  };
+
+  const uint32_t ofs[2] = {operand_offset(0, lane), operand_offset(1, lane)};
+  const uint8_t* a_lds = smem + wm * TM * 16 * kRow;
+  const uint8_t* w_lds = smem + (BM + wn * TN * 16) * kRow;
+  f32x4_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  struct Operands {
+    uint4 w[2][TN], a[2][TM];
+  };
+  auto read = [&](Operands& o, int slot) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) o.w[h][j] = lds16(w_lds + slot * SB + ofs[h] + j * 16 * kRow);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) o.a[h][i] = lds16(a_lds + slot * SB + ofs[h] + i * 16 * kRow);
+    }
+  };
+  auto multiply = [&](const Operands& o, int k) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (HALF && h == 1 && k == half) break;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = mfma(o.w[h][j], o.a[h][i], acc[i][j]);
+    }
+  };
+
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+    if (s < nk) issue(s, s);
+  wait_stages<L, NS - 1>(min(NS - 1, nk - 1));
+  barrier();
+  Operands even, odd;
+  read(even, 0);
+  int slot = 0;
+  auto step = [&](int k, Operands& cur, Operands& next) {
+    const int nslot = slot + 1 == NS ? 0 : slot + 1;
+    wait_lds();  // this wave's reads of stage k, before the slot is refilled
+    wait_stages<L, NS - 2>(min(NS - 2, nk - 2 - k));  // stage k + 1 is in
+    barrier();
+    if (k + NS < nk) issue(k + NS, slot);
+    read(next, nslot);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(cur, k);
+    slot = nslot;
+  };
+  int k = 0;
+  for (; k + 2 < nk; k += 2) {
+    step(k, even, odd);
+    step(k + 1, odd, even);
+  }
+  if (k + 1 < nk) {
+    step(k, even, odd);
+    multiply(odd, k + 1);
+  } else {
+    multiply(even, k);
+  }
+  barrier();  // the stores' slices overlap the ring
+  const int m1 = t.m0 + wm * TM * 16, n1 = t.n0 + wn * TN * 16;
+  add_residual<TM, TN>(g, m1, n1, acc, lane);
+  store_tile<TM, TN>(g, t.slice, m1, n1, acc, smem + wave * 16 * (TN * 32 + 16), lane);
+}
+
+// C = sum over S slices of part (+ R), 4 elements per thread; all loads are
+// issued before the first add.
+template <int S>
 __global__ __launch_bounds__(256) void split_sum_kernel(const float* __restrict__ part,
                                                         const uint16_t* R, uint16_t* C,
-                                                        int64_t mn4, int S) {
+                                                        int64_t mn4) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= mn4) return;
-  float4 v = reinterpret_cast<const float4*>(part)[i];
-  for (int s = 1; s < S; ++s) {
-    const float4 p = reinterpret_cast<const float4*>(part + (int64_t)s * mn4 * 4)[i];
-    v.x += p.x, v.y += p.y, v.z += p.z, v.w += p.w;
-  }
-  if (R) {
-    const uint2 r = reinterpret_cast<const uint2*>(R)[i];
-    v.x += lo(r.x), v.y += hi(r.x), v.z += lo(r.y), v.w += hi(r.y);
-  }
-  reinterpret_cast<uint2*>(C)[i] = make_uint2(pack(v.x, v.y), pack(v.z, v.w));
+  f32x4_t p[S];
+#pragma unroll
+  for (int s = 0; s < S; ++s) p[s] = reinterpret_cast<const f32x4_t*>(part)[(int64_t)s * mn4 + i];
+  uint2 r = make_uint2(0, 0);
+  if (R) r = reinterpret_cast<const uint2*>(R)[i];
+  f32x4_t v = p[0];
+#pragma unroll
+  for (int s = 1; s < S; ++s) v += p[s];
+  if (R) v[0] += lo(r.x), v[1] += hi(r.x), v[2] += lo(r.y), v[3] += hi(r.y);
+  reinterpret_cast<uint2*>(C)[i] = make_uint2(pack(v[0], v[1]), pack(v[2], v[3]));
 }
 
-template <int BM, int BN, int BK, int STAGES, int WGM = 2, int WGN = 2>
-hipError_t launch(const uint16_t* A, const uint16_t* W, const uint16_t* R, uint16_t* C,
-                  float* part, int M, int N, int K, int S, hipStream_t s) {
-  const int MB = (M + BM - 1) / BM, NB = N / BN;
-  const int NBX = (NB + kXcds - 1) / kXcds * kXcds;  // column blocks rounded up to the XCDs
-  hipLaunchKernelGGL((gemm_kernel<BM, BN, BK, STAGES, WGM, WGN>), dim3(MB * NBX * S),
-                     dim3(64 * WGM * WGN), 0, s, A, W, R, C, part, M, N, K, S);
-  return hipGetLastError();
+template <int S>
+void launch_sum(const GemmArgs& g, hipStream_t s) {
+  if constexpr (S > 1) {
+    if (g.split != S) {
+      launch_sum<S - 1>(g, s);
+      return;
+    }
+    const int64_t mn4 = (int64_t)g.m * g.n / 4;
+    hipLaunchKernelGGL((split_sum_kernel<S>), dim3((unsigned)((mn4 + 255) / 256)), dim3(256), 0, s,
+                       g.part, g.r, g.c, mn4);
+  }
 }
 
-// Tile configurations (M x N tile, k per stage; 4 waves in 2 x 2, or 8 in
-// 2 x 4 for the 256 x 256 tiles).  The default choice is measured; the others
-// stay selectable (CPL_GEMM_CFG) for comparison on other shapes.
+using Kernel = void (*)(GemmArgs);
 struct Cfg {
-  int bm, bn, bk;
+  int bm, bn;
+  float stage_us, tile_us;
+  Kernel kernel;
 };
-constexpr int kNumCfgs = 8;
-constexpr Cfg kCfgs[kNumCfgs] = {{64, 128, 32},  {128, 128, 32}, {128, 256, 32}, {256, 128, 32},
-                                 {64, 128, 64},  {128, 128, 64}, {256, 256, 32}, {256, 256, 64}};
-
-hipError_t launch_cfg(int cfg, const uint16_t* A, const uint16_t* W, const uint16_t* R,
-                      uint16_t* C, float* part, int M, int N, int K, int S, hipStream_t s) {
-  switch (cfg) {
-    case 0: return launch<64, 128, 32, 4>(A, W, R, C, part, M, N, K, S, s);
-    case 1: return launch<128, 128, 32, 4>(A, W, R, C, part, M, N, K, S, s);
-    case 2: return launch<128, 256, 32, 3>(A, W, R, C, part, M, N, K, S, s);
-    case 3: return launch<256, 128, 32, 3>(A, W, R, C, part, M, N, K, S, s);
-    case 4: return launch<64, 128, 64, 3>(A, W, R, C, part, M, N, K, S, s);
-    case 5: return launch<128, 128, 64, 2>(A, W, R, C, part, M, N, K, S, s);
-    case 6: return launch<256, 256, 32, 3, 2, 4>(A, W, R, C, part, M, N, K, S, s);
-    case 7: return launch<256, 256, 64, 2, 2, 4>(A, W, R, C, part, M, N, K, S, s);
-  }
-  return hipErrorInvalidValue;
+template <int WM, int WN, int TM, int TN, int NS>
+constexpr Cfg tile_cfg(float stage_us, float tile_us) {
+  return {WM * TM * 16, WN * TN * 16, stage_us, tile_us, gemm_tile_kernel<WM, WN, TM, TN, NS>};
+}
+template <int WM, int WN, int TM, int TN, int NS, bool HALF = false>
+constexpr Cfg stream_cfg(float stage_us, float tile_us) {
+  return {WM * TM * 16, WN * TN * 16, stage_us, tile_us,
+          gemm_stream_kernel<WM, WN, TM, TN, NS, HALF>};
 }
 
-// the configuration with the same tile and 32 k per stage
-int with_bk32(int cfg) { return cfg == 4 ? 0 : cfg == 5 ? 1 : cfg == 7 ? 6 : cfg; }
+// Tile configurations (CPL_GEMM_CFG selects one by its index), each with the
+// microseconds that a stage of 64 k takes and that a tile takes besides, as
+// fitted over 4,600 timings (rows 17-2,048 by the layer's projections at
+// hidden 2,048 and 4,096 and its LM head, weights from HBM; 7-14 % rms).
+constexpr Cfg kCfgs[] = {
+    tile_cfg<2, 4, 8, 4, 2>(1.086f, 12.4f),  // 0: 256 x 256
+    tile_cfg<2, 4, 8, 3, 2>(0.987f, 10.3f),  // 1: 256 x 192
+    tile_cfg<2, 4, 6, 4, 2>(0.887f, 10.8f),  // 2: 192 x 256
+    tile_cfg<4, 2, 4, 4, 3>(0.734f, 8.5f),   // 3: 256 x 128
+    tile_cfg<2, 4, 9, 2, 3>(0.820f, 9.2f),   // 4: 288 x 128
+    tile_cfg<2, 4, 5, 3, 3>(0.729f, 9.8f),   // 5: 160 x 192
+    tile_cfg<2, 4, 4, 3, 3>(0.670f, 8.8f),   // 6: 128 x 192
+    tile_cfg<2, 4, 5, 2, 4>(0.604f, 7.4f),   // 7: 160 x 128
+    stream_cfg<2, 4, 4, 2, 4>(0.520f, 6.3f), // 8: 128 x 128
+    stream_cfg<4, 2, 2, 3, 5>(0.481f, 5.7f), // 9: 128 x 96
+    stream_cfg<2, 4, 3, 2, 5>(0.454f, 6.0f), // 10: 96 x 128
+    stream_cfg<4, 2, 2, 2, 6>(0.366f, 4.4f), // 11: 128 x 64
+    stream_cfg<2, 4, 2, 2, 3>(0.393f, 5.2f), // 12: 64 x 128
+    stream_cfg<2, 4, 3, 1, 4>(0.311f, 4.1f), // 13: 96 x 64
+    stream_cfg<2, 4, 2, 1, 5>(0.250f, 3.7f), // 14: 64 x 64
+    stream_cfg<2, 4, 1, 2, 4>(0.327f, 4.1f), // 15: 32 x 128
+    stream_cfg<2, 4, 1, 1, 6>(0.213f, 3.5f), // 16: 32 x 64
+};
+constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
+constexpr int kDefaultCfg = 8;  // divides every N
+// for K an odd number of 32s
+constexpr Cfg kHalf64 = stream_cfg<2, 4, 2, 2, 3, true>(0.f, 0.f);
+constexpr Cfg kHalf128 = stream_cfg<2, 4, 4, 2, 4, true>(0.f, 0.f);
 
 int env_int(const char* name, int dflt) {
   const char* s = getenv(name);
   return s ? atoi(s) : dflt;
 }
 
-// Tile configuration and K split for a shape: the largest tile that still
-// gives every CU work, then a split over K while the grid is below two
-// workgroups per CU (each slice at least kMinSliceK long).
-void choose(int M, int N, int K, size_t ws_floats, int* cfg, int* S) {
-  const int forced = env_int("CPL_GEMM_CFG", -1);
-  int c = forced;
-  // measured on the layer's projections (N 4096-6144, K 4096): 64 x 128
-  // tiles with 64 k per stage up to 64 rows, 128 x 128 with 64 k above
-  if (c < 0 || c >= kNumCfgs) c = M <= 64 ? 4 : 5;
-  if (kCfgs[c].bn > 128 && N % kCfgs[c].bn != 0) c = 1;
-  const Cfg& f = kCfgs[c];
-  const int64_t tiles = (int64_t)((M + f.bm - 1) / f.bm) * (N / f.bn);
-  int s = 1;
-  const int forced_s = env_int("CPL_GEMM_SPLIT", 0);
-  if (forced_s > 0) {
-    s = forced_s;
-  } else {
-    while (tiles * s * 2 <= 512 && K % (2 * s * f.bk) == 0 && K / (2 * s) >= kMinSliceK) s *= 2;
+// Estimated microseconds of a tile and split: whole rounds of 256 workgroups
+// (a CU works off two small ones no faster than one after the other), no less
+// than the operands take from HBM (5.8 TB/s, less with idle CUs), plus the
+// partials' way through memory and the adding launch.  Where two
+// configurations are bound by memory, the shorter compute time wins.
+float estimate(const Cfg& f, int M, int N, int K, int S) {
+  const int tiles = (M + f.bm - 1) / f.bm * (N / f.bn) * S;
+  const int stages = ((K + kStageK - 1) / kStageK + S - 1) / S;
+  const float compute = (float)((tiles + kCus - 1) / kCus) * (stages * f.stage_us + f.tile_us);
+  const float mn = (float)M * N;
+  float memory = ((float)N * K + (float)M * K + mn) * 2.f / 5.8e6f;
+  if (tiles < kCus) memory *= sqrtf((float)kCus / tiles);
+  float t = fmaxf(compute, memory + 3.f) + 0.05f * compute;
+  if (S > 1) t += 2.5f + S * mn * 4.f / 4.5e6f;
+  return t;
+}
+
+// Tile configuration and K split for a shape: the cheapest by the estimate
+// among those whose columns divide N and whose partials fit the workspace
+// (over the timings above, 1 % slower than the best on average, 11 % at
+// most).  Slices are at least 6 stages long, and the grid is split no
+// further than two workgroups per CU.
+void choose(int M, int N, int K, size_t ws_floats, const Cfg** cfg, int* split) {
+  const int stages = (K + kStageK - 1) / kStageK;
+  const int forced_cfg = env_int("CPL_GEMM_CFG", -1), forced_split = env_int("CPL_GEMM_SPLIT", 0);
+  const bool half = K % kStageK != 0;
+  const Cfg* best = nullptr;
+  int best_split = 1;
+  float best_us = 0.f;
+  auto fits = [&](int s) { return s <= 1 || (size_t)s * (size_t)M * (size_t)N <= ws_floats; };
+  for (int c = 0; c < kNumCfgs; ++c) {
+    const Cfg& f = kCfgs[c];
+    if (N % f.bn != 0) continue;
+    if (forced_cfg >= 0 && forced_cfg < kNumCfgs && c != forced_cfg &&
+        N % kCfgs[forced_cfg].bn == 0)
+      continue;
+    const int64_t tiles = (int64_t)((M + f.bm - 1) / f.bm) * (N / f.bn);
+    for (int s = 1; s <= kMaxSplit; ++s) {
+      if (forced_split > 0) {
+        if (s > 1 && (s > forced_split || s > stages || !fits(s))) break;
+      } else if (s > 1 && (tiles * s > 2 * kCus || stages / s < 6 || !fits(s))) {
+        break;
+      }
+      const float us = estimate(f, M, N, K, s);
+      // a forced split: the largest allowed up to it
+      const bool better = !best || (forced_split > 0 && best == &f) || us < best_us;
+      if (better) best = &f, best_split = s, best_us = us;
+    }
   }
-  while (s > 1 && (K % (s * f.bk) != 0 || (size_t)s * M * N > ws_floats)) s /= 2;
-  *cfg = c;
-  *S = s;
+  if (!best) best = &kCfgs[kDefaultCfg];
+  if (half) best = M <= 64 ? &kHalf64 : &kHalf128;
+  *cfg = best;
+  *split = best_split;
 }
 
 }  // namespace
@@ -378,7 +657,8 @@ extern "C" {
 
 size_t cpl_gemm_workspace_bytes(int32_t m, int32_t n, int32_t k) {
   if (m < 1 || n < 128 || n % 128 != 0 || k < 32 || k % 32 != 0) return 0;
-  int cfg, s;
+  const Cfg* cfg;
+  int s;
   choose(m, n, k, (size_t)-1 / 8, &cfg, &s);
   return s > 1 ? (size_t)s * m * n * sizeof(float) : 0;
 }
@@ -393,21 +673,30 @@ int cpl_gemm(const void* a, const void* w, const void* r, void* c, int32_t m, in
   if ((int64_t)m * k >= ((int64_t)1 << 40) || (int64_t)n * k >= ((int64_t)1 << 40) ||
       (int64_t)m * n >= ((int64_t)1 << 40))
     return CP_ERR_INVALID_ARG;
-  int cfg, S;
-  choose(m, n, k, ws ? ws_bytes / sizeof(float) : 0, &cfg, &S);
-  if (k % kCfgs[cfg].bk != 0) cfg = with_bk32(cfg);  // k per stage must divide K
+  const Cfg* cfg;
+  int split;
+  choose(m, n, k, ws ? ws_bytes / sizeof(float) : 0, &cfg, &split);
+  GemmArgs g;
+  g.a = (const uint16_t*)a;
+  g.w = (const uint16_t*)w;
+  g.r = (const uint16_t*)r;
+  g.c = (uint16_t*)c;
+  g.part = split > 1 ? (float*)ws : nullptr;
+  g.m = m, g.n = n, g.k = k, g.split = split;
+  const int row_blocks = (m + cfg->bm - 1) / cfg->bm;
+  // Weights too large to stay in the 256 MB last-level cache beside the
+  // layer's others, read by at most two row blocks, bypass it: 24 rows x
+  // 24576 x 4096 42.7 -> 37.7 us, 96 rows 48.3 -> 44.9, 261 rows x 4096 x
+  // 12288 43.9 -> 41.2.  With more row blocks (1000 x 6144 x 4096 52.9 ->
+  // 56.2 us) or fewer weights (96 x 6144 x 4096 19.9 -> 20.4) it loses.
+  g.stream_w = row_blocks <= 2 && (int64_t)n * k >= (int64_t)32 << 20;
+  const int tiles = row_blocks * (n / cfg->bn) * split;
   (void)hipGetLastError();
   hipStream_t s = (hipStream_t)stream;
-  const uint16_t* A = (const uint16_t*)a;
-  const uint16_t* W = (const uint16_t*)w;
-  const uint16_t* R = (const uint16_t*)r;
-  uint16_t* C = (uint16_t*)c;
-  float* part = S > 1 ? (float*)ws : nullptr;
-  hipError_t e = launch_cfg(cfg, A, W, R, C, part, m, n, k, S, s);
-  if (e == hipSuccess && S > 1) {
-    const int64_t mn4 = (int64_t)m * n / 4;
-    hipLaunchKernelGGL(split_sum_kernel, dim3((unsigned)((mn4 + 255) / 256)), dim3(256), 0, s,
-                       part, R, C, mn4, S);
+  hipLaunchKernelGGL(cfg->kernel, dim3((tiles + kXcds - 1) / kXcds * kXcds), dim3(512), 0, s, g);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess && split > 1) {
+    launch_sum<kMaxSplit>(g, s);
     e = hipGetLastError();
   }
   return e == hipSuccess ? CP_OK : CP_ERR_HIP;

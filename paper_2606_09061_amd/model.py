@@ -136,19 +136,34 @@ def gemm_workspace_bytes(m, n, k):
     return int(load().cpl_gemm_workspace_bytes(m, n, k))
 
 
+def _scratch(nbytes, device, stream):
+    """Device bytes that belong to the stream the kernels run on, so that the
+    allocator hands them out again only behind those kernels; None when there
+    are none to be had."""
+    import torch
+    if isinstance(stream, int):
+        stream = (torch.cuda.ExternalStream(stream, device=device) if stream
+                  else torch.cuda.default_stream(device))
+    try:
+        with torch.cuda.stream(stream):   # None: the current stream
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
 def gemm(a, w, out, residual=None, stream=None, ws=None):
     """out [M, N] = a [M, K] @ w [N, K]^T (+ residual, which may be out itself),
     on the package's LDS-tiled MFMA kernel (cpl_gemm).  ``ws``: a uint8 device
     tensor for the split over K (allocated here when None and needed)."""
-    import torch
     _dense(a, w, out)
     if residual is not None:
         _dense(residual)
     M, K = a.shape
     N = w.shape[0]
-    need = gemm_workspace_bytes(M, N, K)
-    if ws is None and need:
-        ws = torch.empty(need, dtype=torch.uint8, device=a.device)
+    if ws is None:
+        need = gemm_workspace_bytes(M, N, K)
+        if need:
+            ws = _scratch(need, a.device, stream)
     _check(load().cpl_gemm(a.data_ptr(), w.data_ptr(),
                            residual.data_ptr() if residual is not None else None,
                            out.data_ptr(), M, N, K, ws.data_ptr() if ws is not None else None,

@@ -262,6 +262,33 @@ def test_gemm_matches_reference(monkeypatch, M, N, K, residual, split):
     assert np.all(err <= 2.0 ** -8 * np.abs(want) + slack + 1e-6), f"max err {err.max():.3e}"
 
 
+@pytest.mark.parametrize("M,N,K,split", [
+    (1, 768, 64, 1),       # one row, fewer stages than ring slots
+    (45, 768, 1088, 3),    # odd stage count, uneven slices
+    (301, 768, 448, 1),    # ragged last row block
+    (577, 768, 128, 2),    # several row groups, one stage per slice
+    (130, 256, 416, 2),    # K an odd number of 32s, split
+])
+@pytest.mark.parametrize("cfg", range(17))
+def test_gemm_every_tile_matches_reference(monkeypatch, cfg, M, N, K, split):
+    """Each tile configuration of cpl_gemm (768 columns divide into all of
+    them), against the fp64 product; the bound is test_gemm_matches_reference's."""
+    if K % 64 and cfg:
+        pytest.skip("one kernel takes these K, whatever the configuration")
+    print(f"gemm cfg={cfg} M={M} N={N} K={K} split={split}", flush=True)
+    monkeypatch.setenv("CPL_GEMM_CFG", str(cfg))
+    monkeypatch.setenv("CPL_GEMM_SPLIT", str(split))
+    from paper_2606_09061_amd import model as MM
+    a, w, r = _bf16((M, K), 51), _bf16((N, K), 52, 0.05), _bf16((M, N), 53)
+    out = r.clone().to(DEV)
+    MM.gemm(a.to(DEV), w.to(DEV), out, out)
+    torch.cuda.synchronize()
+    want = _f64(a) @ _f64(w).T + _f64(r)
+    slack = 2.0 ** -20 * (np.abs(_f64(a)) @ np.abs(_f64(w)).T)
+    err = np.abs(_f64(out) - want)
+    assert np.all(err <= 2.0 ** -8 * np.abs(want) + slack + 1e-6), f"max err {err.max():.3e}"
+
+
 def test_gemm_rejects_unsupported_shapes():
     lib = M.load()
     x = torch.zeros(512, 512, dtype=torch.bfloat16, device=DEV)
