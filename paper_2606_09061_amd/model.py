@@ -9,11 +9,10 @@ scheduler's batch through every layer of such a model with synthetic weights:
     cpl_swiglu -> down GEMM (+ residual)] -> RMSNorm -> LM head on each row's
     last token -> argmax
 
-Projections of small batches (up to 32 tokens) run in this package's skinny
-GEMM kernel, the rest as library GEMMs (torch.mm / addmm, i.e. hipBLASLt);
-every other step runs in this package's HIP kernels
-(libcplayer.so for the element-wise parts, libcpattn.so for append and
-attention).  Each layer has
+Every step runs in this package's HIP kernels (libcplayer.so for the
+projections and the element-wise parts, libcpattn.so for append and
+attention); projections of shapes or tensors that those do not take run as
+library GEMMs (torch.mm / addmm, i.e. hipBLASLt).  Each layer has
 its own paged KV pool; all layers share one block table, whose row s maps
 slot s's logical blocks to physical blocks (a random permutation, so pages
 are scattered).  Weights are N(0, 0.02) in bf16, norms 1.
@@ -119,6 +118,21 @@ def skinny_faster(m, n, k):
     return m <= 32
 
 
+# Where, of those, the skinny kernel beats the tiled one too.  Per launch,
+# weights from HBM, skinny / tiled us: QKV (6144 x 4096) 11.4 / 13.0 at 1 row,
+# 11.9 / 13.8 at 16, 13.1 / 14.2 at 24, 14.8 / 14.6 at 32; gate/up (24576 x
+# 4096) 31.3 / 36.5, 33.4 / 37.3, 37.9 / 38.0, 42.3 / 39.5.  Long rows (K > N:
+# the down projection) need more workgroups than their column slices give,
+# which the tiled kernel's split over K has: 4096 x 12288 21.1 / 19.3 at 8
+# rows, 21.9 / 19.8 at 16, 31.3 / 21.0 at 32; 2048 x 6144 10.8 / 9.2 at 8
+# (20.4 / 19.7 at 1 row, where its second launch costs as much on the host).
+# Wide projections stream their activations again for every slice and lose
+# from 17 rows (LM head, 151936 x 4096: 196.7 / 192.1 at 16, 209.2 / 193.8 at
+# 20).  The tiled kernel takes N % 128 == 0 only.
+def _skinny_over_tiled(m, n, k):
+    return n % 128 != 0 or m < 8 or (k <= n and (m <= 16 or (m <= 24 and n < 8192)))
+
+
 def gemm_skinny(a, w, out, residual=None, stream=None):
     """out [M, N] = a [M, K] @ w [N, K]^T (+ residual, which may be out itself)."""
     _dense(a, w, out)
@@ -170,13 +184,17 @@ def gemm(a, w, out, residual=None, stream=None, ws=None):
                            ws.numel() if ws is not None else 0, _s(stream)), "cpl_gemm")
 
 
+def _aligned(*ts):
+    return all(t is None or t.data_ptr() % 16 == 0 for t in ts)
+
+
 def project_attn(a, w, out, residual=None, stream=None, ws=None):
     """The QKV and output projections around the attention step, always on
-    the package's kernels: the skinny kernel up to 32 rows, the tiled MFMA
-    GEMM above (``ws``: its split-K workspace, see gemm)."""
+    the package's kernels: the skinny kernel for the smallest batches, the
+    tiled MFMA GEMM above (``ws``: its split-K workspace, see gemm)."""
     M, K = a.shape
     N = w.shape[0]
-    if skinny_faster(M, N, K):
+    if skinny_faster(M, N, K) and (_skinny_over_tiled(M, N, K) or not _aligned(out, residual)):
         gemm_skinny(a, w, out, residual, stream)
     elif N % 128 == 0 and K % 32 == 0:
         gemm(a, w, out, residual, stream, ws)
@@ -184,14 +202,45 @@ def project_attn(a, w, out, residual=None, stream=None, ws=None):
         raise ValueError(f"projection {M}x{N}x{K}: the kernels need N % 128 == 0 and K % 32 == 0")
 
 
-def project(a, w, out, residual=None, stream=None):
-    """a @ w^T into out (+ residual): the skinny kernel where it is faster
-    (small batches, moderate projections), the platform BLAS otherwise.
-    The feed-forward and LM-head projections use it."""
+def _tiled_takes(a, w, out, residual):
+    """Whether cpl_gemm can stand in for torch.mm / addmm here: plain dense
+    bf16 matrices of matching shapes on the current GPU, 16-byte aligned, that
+    autograd does not follow.  Everything else is left to torch, which
+    computes or refuses it."""
+    import torch
+    ts = (a, w, out) if residual is None else (a, w, out, residual)
+    for t in ts:
+        if (type(t) not in (torch.Tensor, torch.nn.Parameter) or t.dtype != torch.bfloat16
+                or t.dim() != 2 or not t.is_cuda or t.device != a.device
+                or not t.is_contiguous() or t.data_ptr() % 16
+                or (t.requires_grad and torch.is_grad_enabled())):
+            return False
+    M, K = a.shape
+    N = w.shape[0]
+    return (M > 0 and w.shape[1] == K and out.shape == (M, N) and N % 128 == 0 and K % 32 == 0
+            and K > 0 and N > 0 and (residual is None or residual.shape == out.shape)
+            and out.data_ptr() not in (a.data_ptr(), w.data_ptr())
+            and a.device.index == torch.cuda.current_device())
+
+
+def project(a, w, out, residual=None, stream=None, ws=None):
+    """a @ w^T into out (+ residual), on the package's kernels like
+    project_attn where they take the shapes and tensors, else on the platform
+    BLAS.  The feed-forward and LM-head projections use it.
+
+    The tiled kernel against hipBLASLt (weights from HBM): gate/up (24576 x
+    4096) 44.9 -> 38.0 us at 24 rows, 48.9 -> 45.5 at 96, 72.2 -> 65.7 at 261,
+    164.4 -> 161.9 at 1,000, 279.6 -> 294.0 at 2,048; down (4096 x 12288) 24.8
+    -> 20.3, 55.9 -> 28.6, 67.4 -> 44.0, 115.4 -> 92.9, 180.9 -> 160.2."""
     import torch
     M, K = a.shape
     N = w.shape[0]
-    if skinny_faster(M, N, K):
+    skinny = skinny_faster(M, N, K)
+    if skinny and _skinny_over_tiled(M, N, K):
+        gemm_skinny(a, w, out, residual, stream)
+    elif _tiled_takes(a, w, out, residual):
+        gemm(a, w, out, residual, stream, ws)
+    elif skinny:
         gemm_skinny(a, w, out, residual, stream)
     elif residual is None:
         torch.mm(a, w.t(), out=out)
@@ -293,7 +342,7 @@ class Model:
         self.pos = torch.zeros(T, dtype=torch.int32, device=self.dev)
         self.tokens = torch.randint(0, c.vocab, (T,), generator=gen, device=self.dev)
         self.ws = torch.empty(64 << 20, dtype=torch.uint8, device=self.dev)      # attention plan
-        # split-K partials of the QKV / output projections (grown on demand)
+        # split-K partials of the projections (grown on demand)
         self.ws_gemm = torch.empty(256, dtype=torch.uint8, device=self.dev)
         # an append item covers one row's tokens inside one block: at most
         # max_tokens + max_seqs items of 16 bytes, so the append never needs more
@@ -334,8 +383,13 @@ class Model:
                 self.ws = torch.empty(cp.workspace_bytes(self.desc, rows), dtype=torch.uint8,
                                       device=self.dev)
                 plan = cp.attn_prepare(self.desc, rows, self.ws, stream=s)
+            n_last = int((rows[:, 2] > 0).sum())
             need = max(gemm_workspace_bytes(T, qkv.shape[1], c.hidden),
-                       gemm_workspace_bytes(T, c.hidden, c.hq * c.head_dim)) if T > 32 else 0
+                       gemm_workspace_bytes(T, c.hidden, c.hq * c.head_dim),
+                       gemm_workspace_bytes(T, 2 * c.inter, c.hidden),
+                       gemm_workspace_bytes(T, c.hidden, c.inter),
+                       gemm_workspace_bytes(n_last, c.vocab, c.hidden)
+                       if self.lm_head is not None else 0)
             if need > self.ws_gemm.numel():
                 self.ws_gemm = torch.empty(need, dtype=torch.uint8, device=self.dev)
             for L, kc, vc in zip(self.layers, self.kc, self.vc):
@@ -347,9 +401,9 @@ class Model:
                 cp.attn_run(plan, q, kc, vc, self.bt, attn, self.ws, stream=s)
                 project_attn(attn.view(T, c.hq * c.head_dim), L["o"], x, x, s, self.ws_gemm)
                 rmsnorm(x, L["post_norm"], h, c.eps, s)
-                project(h, L["gate_up"], gu, None, s)
+                project(h, L["gate_up"], gu, None, s, self.ws_gemm)
                 swiglu(gu, act, s)
-                project(act, L["down"], x, x, s)
+                project(act, L["down"], x, x, s, self.ws_gemm)
             if self.lm_head is None:
                 return None
             last = torch.from_numpy(np.cumsum(rows[:, 2]).astype(np.int64) - 1)
@@ -357,7 +411,7 @@ class Model:
             hl = torch.empty(len(last), c.hidden, dtype=torch.bfloat16, device=self.dev)
             rmsnorm(x.index_select(0, last), self.final_norm, hl, c.eps, s)
             logits = torch.empty(len(last), c.vocab, dtype=torch.bfloat16, device=self.dev)
-            project(hl, self.lm_head, logits, None, s)
+            project(hl, self.lm_head, logits, None, s, self.ws_gemm)
             return torch.argmax(logits, dim=-1)
 
 
