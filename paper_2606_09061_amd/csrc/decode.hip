@@ -9,7 +9,7 @@
 namespace cpattn {
 
 template <int D, int B, int G>
-__global__ __launch_bounds__(256, G * D >= 512 ? 3 : 4) void decode_kernel(
+__global__ __launch_bounds__(256, decode_impl::kOnMfma<G> ? 2 : 4) void decode_kernel(
     const DecodeItem* __restrict__ items, const uint16_t* __restrict__ q,
     const uint16_t* __restrict__ k_cache, const uint16_t* __restrict__ v_cache,
     const int32_t* __restrict__ bt, uint16_t* __restrict__ out, float* __restrict__ part_o,

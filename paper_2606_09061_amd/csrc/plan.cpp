@@ -320,6 +320,7 @@ Tuning tuning_from_env(int num_cus) {
   if (const char* s = std::getenv("CP_PREFILL_TARGET_ITEMS")) t.prefill_target_items = atoi(s);
   if (const char* s = std::getenv("CP_PREFILL_MIN_SPLIT")) t.prefill_min_split = std::max(1, atoi(s));
   if (const char* s = std::getenv("CP_FUSE_DECODE")) t.fuse_decode = std::min(4, std::max(0, atoi(s)));
+  if (const char* s = std::getenv("CP_DECODE_UNITS_PER_CU")) t.decode_units_per_cu = atof(s);
   if (const char* s = std::getenv("CP_FUSE_SPREAD")) t.fuse_spread = atof(s);
   if (const char* s = std::getenv("CP_FUSE_KEYS_PER_STEP")) t.fuse_keys_per_step = atof(s);
   if (const char* s = std::getenv("CP_FUSE_NARROW")) t.fuse_narrow = atoi(s) != 0;
@@ -457,8 +458,26 @@ static int64_t choose_split_steps(const cp_attn_desc& d, const Tuning& t,
   return best_s;
 }
 
-void build_plan(const cp_attn_desc& d, const cp_row_meta* rows, int32_t n_rows, const Tuning& t,
-                Plan& p) {
+// The settings that depend on how a decode unit runs.  On the matrix cores a
+// unit streams faster beside tiles, so it counts as less of a tile's time,
+// and the kernel keeps two workgroups per CU instead of four.  Measured, step
+// us of the 512-token budget mix | 2k-token prefill-heavy mix | 64/8-head
+// replay round, at units per CU of a prefill-dominated fused step x keys per
+// tile step: 0.5 x 68 153 | 641 | 130-133, 0.5 x 74 156 | 636 | 131, 0.5 x 76
+// 156 | 631 | 130, 0.5 x 80 161 | 619-641 | 125-130, 0.5 x 100 166 | 641 |
+// 130, 0.55 x 76 156 | 633 | 136, 0.75 x 80 161 | 640 | 138, 1.5 x 80 160 |
+// 653 | 132; the vector units' kernel and settings 160 | 645 | 148-153.
+// (Whole rows outlast the tiles at 0.25 to 0.375 units per CU.)
+static Tuning resolve_tuning(Tuning t, int G) {
+  const bool mfma = G >= kDecodeMfmaMinGroup;
+  if (t.decode_units_per_cu <= 0.0) t.decode_units_per_cu = mfma ? 2.0 : 3.0;
+  if (t.fuse_units_per_cu <= 0.0) t.fuse_units_per_cu = mfma ? 0.5 : 0.75;
+  if (t.fuse_keys_per_step <= 0.0) t.fuse_keys_per_step = mfma ? 75.0 : 64.0;
+  return t;
+}
+
+void build_plan(const cp_attn_desc& d, const cp_row_meta* rows, int32_t n_rows,
+                const Tuning& settings, Plan& p) {
   PlanScratch& sc = p.scratch;
   p.prefill.clear();
   p.prefill_wide.clear();
@@ -467,6 +486,7 @@ void build_plan(const cp_attn_desc& d, const cp_row_meta* rows, int32_t n_rows, 
   p.partial_rows = 0;
   p.decode_split_blocks = 0;
   const int G = d.num_q_heads / d.num_kv_heads;
+  const Tuning t = resolve_tuning(settings, G);
   const int Hkv = d.num_kv_heads;
   const int B = d.block_size;
   const int tile_tok = kPrefillRows / G;
@@ -536,13 +556,18 @@ void build_plan(const cp_attn_desc& d, const cp_row_meta* rows, int32_t n_rows, 
     dec_blocks += ceil_div(kv_end, B) * Hkv;
   });
   if (dec_blocks > 0) {
-    // Items per CU grow with the decode bytes: ~3 per CU (the kernel keeps
-    // three workgroups resident) for small loads, where every extra item costs
-    // plan upload, partial rows for the merge and a workgroup's start-up,
-    // rising to 6 per CU at 4 GB and above, where finer items balance the
-    // tail better (measured on the 0.1, 0.8, 1.8 and 5.5 GB mixes).
+    // Items per CU grow with the decode bytes: about what the kernel keeps
+    // resident (2 workgroups per CU on the matrix cores, 3 on the vector
+    // units) for small loads, where every extra item costs plan upload,
+    // partial rows for the merge and a workgroup's start-up, rising to 3 (6)
+    // per CU at 4 GB and above, where finer items balance the tail better.
+    // Step us on the matrix cores at 1 / 1.5 / 2 / 3 / 4 per CU: 8 rows of
+    // 14.9 k keys 25.7 / 24.0 / 24.8 / 26.4 / 30.8; 512-token budget mix (0.88
+    // GB) 153.6 / 153.1 / 152.6 / 156.0 / 159.2; 256 decode rows (7 GB) 1071 /
+    // 1069 / 1088 / 1066 / 1071.
     const double dec_bytes = (double)dec_blocks * B * d.head_dim * 4.0;
-    double per_cu = 3.0 + 3.0 * std::min(1.0, dec_bytes / 4.0e9);
+    const double rise = G >= kDecodeMfmaMinGroup ? 0.5 : 1.0;
+    double per_cu = t.decode_units_per_cu * (1.0 + rise * std::min(1.0, dec_bytes / 4.0e9));
     // Inside a prefill-dominated launch, longer decode ranges: each unit
     // streams beside the tiles for much of the launch.  Only rows longer than
     // the cut are split, so this sets the longest unit (measured best at

@@ -27,6 +27,9 @@ constexpr int kPrefillRowsWide = 256;
 constexpr int kPrefillKeys = 64;
 // Waves per decode workgroup (each wave walks every kDecodeWaves-th block).
 constexpr int kDecodeWaves = 4;
+// Head groups of at least this many q heads run their decode units on the
+// matrix cores (two workgroups per CU), smaller ones on the vector units.
+constexpr int kDecodeMfmaMinGroup = 4;
 // Upper bound of Tuning::prefill_min_len: rows shorter than it become one
 // decode item list per token, which only pays for few-token chunks.
 constexpr int kMaxPrefillMinLen = 64;
@@ -106,9 +109,11 @@ struct Tuning {
                                 // 1 after its tiles, 2 before them, 3 spread among them,
                                 // 4 longest first with them
   double fuse_spread = 1.0;     // mode 3: decode blocks spread over this fraction of the tiles
-  double fuse_keys_per_step = 64.0;  // mode 4: decode keys worth one 64-key step of a tile
+  double fuse_keys_per_step = 0.0;  // mode 4: decode keys worth one 64-key step of a tile (0: by
+                                    // group)
+  double decode_units_per_cu = 0.0;  // decode ranges per CU of small decode loads (0: by group)
   bool fuse_narrow = true;      // a step with decode blocks in its prefill launch: 128-row tiles
-  double fuse_units_per_cu = 0.75;   // decode ranges per CU that set the split length when
+  double fuse_units_per_cu = 0.0;    // decode ranges per CU that set the split length when
                                      // prefill dominates a fused step
   double fuse_flops_per_byte = 180.0;  // prefill dominates: its flops > this x decode bytes
   int xcd_piece_div = 4;        // K/V groups costlier than 1/(this x XCDs) of a launch's work

@@ -59,6 +59,23 @@ def test_geometry_grid(monkeypatch, geom, tiles):
     _full_check(batch, 2000 + len(str(geom)), f"grid {geom}")
 
 
+@pytest.mark.parametrize("items", [0, 1 << 20])
+@pytest.mark.parametrize("hq,hkv,d,b", [(8, 2, 128, 16), (16, 2, 128, 32), (8, 2, 64, 16),
+                                        (8, 1, 64, 32), (4, 2, 128, 32), (2, 2, 64, 16)])
+def test_decode_rows_at_tile_edges(monkeypatch, hq, hkv, d, b, items):
+    """Decode rows whose contexts end at and around the edges of the 16- and
+    32-key tiles, of the four waves' turns and of a block pair; with the
+    largest item count every row is cut into its shortest ranges, so that the
+    merge combines from 1 to 79 splits per row."""
+    if items:
+        monkeypatch.setenv("CP_DECODE_TARGET_ITEMS", str(items))
+    ctx = [1, 2, 15, 16, 17, 31, 32, 33, 47, 49, 63, 64, 65, 127, 128, 129, 159, 161, 255, 257, 511,
+           1000, 1025, 2500, 10000]
+    rng = np.random.default_rng(d + b + hq)
+    batch = make_batch("edges", hq, hkv, d, b, [(c - 1, 1) for c in ctx], rng)
+    _full_check(batch, 2600 + d + b, f"decode edges {hq}/{hkv} D{d} B{b} items={items}")
+
+
 def test_rows_in_any_order_and_zero_length_rows():
     rng = np.random.default_rng(7)
     rows = [(10, 40), (0, 0), (63, 1), (200, 0), (128, 130), (31, 1)]
