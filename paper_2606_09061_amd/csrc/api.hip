@@ -363,6 +363,26 @@ Plan& thread_plan() {
   return p;
 }
 
+// The rows of an append as its kernel's arguments take them; false when there
+// are too many, or when a short span list serves (fewer lookups).
+bool fill_runs(const cp_row_meta* rows, int32_t n_rows, int block_size, const AppendPlan& p,
+               AppendRuns& out, int* n_runs) {
+  if (p.items.size() <= (size_t)kAppendInlineItems) return false;
+  int n = 0;
+  int32_t tok = 0, item = 0;
+  for (int32_t r = 0; r < n_rows; ++r) {
+    const cp_row_meta& m = rows[r];
+    if (m.chunk_len <= 0) continue;
+    if (n == kAppendRuns) return false;
+    out.r[n++] = AppendRun{tok, m.req_id, m.chunk_start, item};
+    tok += m.chunk_len;
+    item += (m.chunk_start + m.chunk_len - 1) / block_size - m.chunk_start / block_size + 1;
+  }
+  out.r[n] = AppendRun{tok, 0, 0, item};
+  *n_runs = n;
+  return true;
+}
+
 AppendPlan& thread_append_plan() {
   thread_local AppendPlan p;
   return p;
@@ -526,6 +546,15 @@ int cp_kv_append(const cp_attn_desc* desc, const void* k_new, const void* v_new,
     a.mbr = desc->max_blocks_per_req;
     const AppendInline* inl = nullptr;
     Stage* st = nullptr;
+    thread_local AppendRuns runs;
+    int n_runs = 0;
+    if (fill_runs(rows, n_rows, desc->block_size, p, runs, &n_runs)) {
+      const long pi = prof_open(0, s);
+      const hipError_t e =
+          launch_append_runs(desc->head_dim, desc->block_size, a, runs, n_runs, PlanCopyArgs{}, s);
+      prof_close(pi, s);
+      return finish(e, s);
+    }
     if (a.n_items <= kAppendInlineItems) {
       thread_local AppendInline buf;
       std::memcpy(buf.items, p.items.data(), p.items.size() * sizeof(AppendItem));
@@ -728,8 +757,11 @@ int cp_step_mixed(const cp_attn_desc* desc, const void* q, const void* k_new, co
   try {
     AppendPlan& ap = thread_append_plan();
     build_append_plan(*desc, rows, n_rows, ap);
-    if (ap.items.size() > (size_t)kAppendInlineItems) {
-      // a long span list is uploaded itself: the two calls in turn
+    thread_local AppendRuns runs;
+    int n_runs = 0;
+    const bool by_rows = fill_runs(rows, n_rows, desc->block_size, ap, runs, &n_runs);
+    if (!by_rows && ap.items.size() > (size_t)kAppendInlineItems) {
+      // a long span list of many rows is uploaded itself: the two calls in turn
       const int ra = cp_kv_append(desc, k_new, v_new, k_cache, v_cache, block_tables, rows,
                                   n_rows, ws, ws_bytes, stream);
       if (ra != CP_OK) return ra;
@@ -742,13 +774,13 @@ int cp_step_mixed(const cp_attn_desc* desc, const void* q, const void* k_new, co
     }
     Plan& p = thread_plan();
     build_plan(*desc, rows, n_rows, tuning_from_env(num_cus_setting()), p);
-    if (ws_bytes < p.ws_bytes) return CP_ERR_WORKSPACE;
+    if (ws_bytes < p.ws_bytes || (by_rows && ws_bytes < ap.ws_bytes)) return CP_ERR_WORKSPACE;
     Stage* st = nullptr;
     uint32_t seq = 0;
     int rc = take_stage(p.plan_bytes, &st, &seq, [&](uint8_t* h) { serialize_into(p, h); });
     if (rc != CP_OK) return rc;
     thread_local AppendInline inl;
-    std::memcpy(inl.items, ap.items.data(), ap.items.size() * sizeof(AppendItem));
+    if (!by_rows) std::memcpy(inl.items, ap.items.data(), ap.items.size() * sizeof(AppendItem));
     AppendArgs a;
     a.items = nullptr;
     a.n_items = (int)ap.items.size();
@@ -767,7 +799,9 @@ int cp_step_mixed(const cp_attn_desc* desc, const void* q, const void* k_new, co
     cpa.seq = seq;
     cpa.n_blocks = std::min(kCopyBlocksMax, (cpa.n16 + 8 * 256 - 1) / (8 * 256));
     const long pi = prof_open(0, s);
-    const hipError_t e = launch_append_copy(desc->head_dim, desc->block_size, a, inl, cpa, s);
+    const hipError_t e =
+        by_rows ? launch_append_runs(desc->head_dim, desc->block_size, a, runs, n_runs, cpa, s)
+                : launch_append_copy(desc->head_dim, desc->block_size, a, inl, cpa, s);
     prof_close(pi, s);
     if (e == hipSuccess) {  // the slot's completion words now belong to this copy
       st->seq = seq;

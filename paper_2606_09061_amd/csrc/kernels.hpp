@@ -15,6 +15,20 @@ struct AppendInline {
   AppendItem items[kAppendInlineItems];
 };
 
+// Longer ones travel as the rows they come from, which the workgroups cut into
+// blocks themselves: up to kAppendRuns rows with tokens (3.9 KB with the other
+// arguments, below the 4 KB limit).
+constexpr int kAppendRuns = 240;
+struct AppendRun {
+  int32_t tok0;   // first new token
+  int32_t req;
+  int32_t start;  // its position
+  int32_t item0;  // append items of the rows before
+};
+struct AppendRuns {
+  AppendRun r[kAppendRuns + 1];  // the entry after the last: total tokens and items
+};
+
 struct AppendArgs {
   const AppendItem* items;
   int n_items;
@@ -64,6 +78,10 @@ hipError_t launch_append(int D, int B, const AppendArgs& a, const AppendInline* 
                          hipStream_t s);
 // the inline append and a plan copy in one launch (256-thread workgroups)
 hipError_t launch_append_copy(int D, int B, const AppendArgs& a, const AppendInline& inl,
+                              const PlanCopyArgs& cp, hipStream_t s);
+// the append of n_runs rows (a.n_items items in all), with a plan copy unless
+// cp.n_blocks is 0
+hipError_t launch_append_runs(int D, int B, const AppendArgs& a, const AppendRuns& runs, int n_runs,
                               const PlanCopyArgs& cp, hipStream_t s);
 hipError_t launch_prefill(int D, int G, const AttnArgs& a, hipStream_t s);
 hipError_t launch_decode(int D, int B, int G, const AttnArgs& a, hipStream_t s);

@@ -458,21 +458,22 @@ static int64_t choose_split_steps(const cp_attn_desc& d, const Tuning& t,
   return best_s;
 }
 
-// The settings that depend on how a decode unit runs.  On the matrix cores a
-// unit streams faster beside tiles, so it counts as less of a tile's time,
-// and the kernel keeps two workgroups per CU instead of four.  Measured, step
-// us of the 512-token budget mix | 2k-token prefill-heavy mix | 64/8-head
-// replay round, at units per CU of a prefill-dominated fused step x keys per
-// tile step: 0.5 x 68 153 | 641 | 130-133, 0.5 x 74 156 | 636 | 131, 0.5 x 76
-// 156 | 631 | 130, 0.5 x 80 161 | 619-641 | 125-130, 0.5 x 100 166 | 641 |
-// 130, 0.55 x 76 156 | 633 | 136, 0.75 x 80 161 | 640 | 138, 1.5 x 80 160 |
-// 653 | 132; the vector units' kernel and settings 160 | 645 | 148-153.
+// The settings that depend on how a decode unit runs.  On the matrix cores the
+// kernel keeps two workgroups per CU instead of four, and a unit beside tiles
+// takes less from them.  Measured, step us of the 512-token budget mix | the
+// 2k-token prefill-heavy mix | the 64/8-head replay round | 1,700 tokens after
+// 4k and 12k keys beside 64 decode rows | 512 tokens after 20k keys beside
+// 100, at units per CU of a prefill-dominated fused step x keys per tile step:
+//   0.5 x 60   154 | 624 | 135 | 285 | 264     0.7 x 60   154 | 612 | 143 | 294 | 266
+//   0.5 x 75   155 | 631 | 133 | 279 | 266     0.7 x 75   155 | 611 | 140 | 309 | 269
+//   0.5 x 90   167 | 613 | 133 | 283 | 270     1.0 x 60   154 | 606 | 145 | 293 | 265
+// and the vector units' kernel with its settings 157 | 625 | 153 | 297 | 291.
 // (Whole rows outlast the tiles at 0.25 to 0.375 units per CU.)
 static Tuning resolve_tuning(Tuning t, int G) {
   const bool mfma = G >= kDecodeMfmaMinGroup;
   if (t.decode_units_per_cu <= 0.0) t.decode_units_per_cu = mfma ? 2.0 : 3.0;
   if (t.fuse_units_per_cu <= 0.0) t.fuse_units_per_cu = mfma ? 0.5 : 0.75;
-  if (t.fuse_keys_per_step <= 0.0) t.fuse_keys_per_step = mfma ? 75.0 : 64.0;
+  if (t.fuse_keys_per_step <= 0.0) t.fuse_keys_per_step = mfma ? 60.0 : 64.0;
   return t;
 }
 
@@ -552,8 +553,10 @@ void build_plan(const cp_attn_desc& d, const cp_row_meta* rows, int32_t n_rows,
   };
   sc.dec_groups.clear();
   int64_t dec_blocks = 0;
+  int32_t dec_longest = 0;
   each_decode_token([&](const cp_row_meta&, int32_t, int32_t kv_end) {
     dec_blocks += ceil_div(kv_end, B) * Hkv;
+    dec_longest = std::max(dec_longest, kv_end);
   });
   if (dec_blocks > 0) {
     // Items per CU grow with the decode bytes: about what the kernel keeps
@@ -581,6 +584,12 @@ void build_plan(const cp_attn_desc& d, const cp_row_meta* rows, int32_t n_rows,
                                : std::max<int64_t>(1, (int64_t)(t.num_cus * per_cu));
     int64_t sb = ceil_div(dec_blocks, target);
     sb = std::max<int64_t>(sb, 8);
+    // Short contexts are not cut: the merge launch costs more than the longer
+    // units (step us, cut / whole: 2 rows of 200 keys and two chunks 14.7 /
+    // 12.2; 16 rows of up to 256 keys 14.8 / 12.5, 32 of up to 512 22.1 / 16.3;
+    // 8 rows of up to 1,024 keys 15.6 / 17.8)
+    if (t.decode_target_items <= 0 && dec_longest <= kDecodeWholeKeys)
+      sb = std::max<int64_t>(sb, ceil_div(dec_longest, B));
     sb = ceil_div(sb, kDecodeWaves) * kDecodeWaves;
     p.decode_split_blocks = (int32_t)sb;
     // with the decode rows inside the prefill launch, their units (in tile

@@ -30,6 +30,8 @@ constexpr int kDecodeWaves = 4;
 // Head groups of at least this many q heads run their decode units on the
 // matrix cores (two workgroups per CU), smaller ones on the vector units.
 constexpr int kDecodeMfmaMinGroup = 4;
+// Decode rows stay whole when none has more keys than this.
+constexpr int kDecodeWholeKeys = 512;
 // Upper bound of Tuning::prefill_min_len: rows shorter than it become one
 // decode item list per token, which only pays for few-token chunks.
 constexpr int kMaxPrefillMinLen = 64;

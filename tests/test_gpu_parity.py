@@ -76,6 +76,30 @@ def test_decode_rows_at_tile_edges(monkeypatch, hq, hkv, d, b, items):
     _full_check(batch, 2600 + d + b, f"decode edges {hq}/{hkv} D{d} B{b} items={items}")
 
 
+@pytest.mark.parametrize("rows,what", [
+    ([(7, 1)] * 239 + [(13, 70)], "240 rows, 245 spans: the rows in the kernel's arguments"),
+    ([(7, 1)] * 240 + [(13, 70)], "241 rows, 246 spans: the span list uploaded"),
+    ([(0, 0), (5, 3200), (0, 0), (16, 17), (31, 1)], "few rows, 204 spans, empty rows"),
+    ([(16 * i + i % 16, 1) for i in range(200)], "200 spans: the span list in the arguments"),
+])
+@pytest.mark.parametrize("one_call", [False, True])
+def test_append_of_many_spans(rows, what, one_call):
+    """The append's three ways of naming its spans, at their limits; pools bit
+    for bit, outputs against the oracle."""
+    batch = make_batch("spans", 4, 2, 64, 16, rows, np.random.default_rng(len(rows)))
+    say(f"[gpu] {what}, one_call={one_call}")
+    tens = make_tensors(batch, seed=2700 + len(rows))
+    kc_ref, vc_ref = oracle.kv_append(batch, tens["k_new"], tens["v_new"], tens["k_cache"],
+                                      tens["v_cache"])
+    ref = oracle.attn(batch, tens["q"], kc_ref, vc_ref)
+    t = to_dev(tens)
+    out = run_step(batch, t, one_call=one_call)
+    torch.cuda.synchronize()
+    assert np.array_equal(words(t["k_cache"]).reshape(-1), kc_ref.reshape(-1)), "K cache differs"
+    assert np.array_equal(words(t["v_cache"]).reshape(-1), vc_ref.reshape(-1)), "V cache differs"
+    assert_close(out, ref, what)
+
+
 def test_rows_in_any_order_and_zero_length_rows():
     rng = np.random.default_rng(7)
     rows = [(10, 40), (0, 0), (63, 1), (200, 0), (128, 130), (31, 1)]
