@@ -225,21 +225,28 @@ void place_decode_blocks(std::vector<PrefillRec>& recs, const std::vector<Decode
 }
 
 // Makespan, in steps, of longest-first list scheduling of `groups` (cost,
-// count) on `slots` identical slots.  Slot loads are kept as a histogram
-// (load, slots) sorted by load, so equal items are placed in bulk.
+// count; longest first) on `slots` identical slots.  Slot loads are kept as a histogram
+// (load, slots) sorted by load, so equal items are placed in bulk.  Returns
+// early, with a makespan above `limit`, once a slot's load exceeds that.
 int64_t lpt_makespan(std::vector<std::pair<int64_t, int64_t>>& groups, int64_t slots,
-                     std::vector<std::pair<int64_t, int64_t>>& load) {
+                     std::vector<std::pair<int64_t, int64_t>>& load, int64_t limit) {
   if (groups.empty()) return 0;
-  std::sort(groups.begin(), groups.end(),
-            [](const std::pair<int64_t, int64_t>& a, const std::pair<int64_t, int64_t>& b) {
-              return a.first > b.first;
-            });
+  // equal costs as one group: the same placement, fewer insertions
+  size_t n = 0;
+  for (const auto& g : groups) {
+    if (n > 0 && groups[n - 1].first == g.first)
+      groups[n - 1].second += g.second;
+    else
+      groups[n++] = g;
+  }
+  groups.resize(n);
   load.assign(1, {0, slots});
   size_t head = 0;  // load[head] is the least-loaded bucket; earlier ones are empty
   for (const auto& g : groups) {
     int64_t k = g.second;
     if (head + 1 == load.size() && k >= slots) {  // all slots level: whole rounds at once
       load[head].first += (k / slots) * g.first;
+      if (load[head].first > limit) return load[head].first;
       k %= slots;
     }
     while (k > 0) {
@@ -247,6 +254,7 @@ int64_t lpt_makespan(std::vector<std::pair<int64_t, int64_t>>& groups, int64_t s
       if ((load[head].second -= take) == 0) ++head;
       // insert `take` slots at load l + g.first, keeping the order
       const int64_t nl = l + g.first;
+      if (nl > limit) return nl;
       auto pos = std::lower_bound(
           load.begin() + head, load.end(), nl,
           [](const std::pair<int64_t, int64_t>& a, int64_t v) { return a.first < v; });
@@ -438,9 +446,22 @@ static int64_t choose_split_steps(const cp_attn_desc& d, const Tuning& t,
         groups.push_back({ceil_div(tl.kv_end - cuts * split_keys, kPrefillKeys) + kItemOverhead, Hkv});
       }
       if (full[w] > 0) groups.push_back({S + kItemOverhead, full[w] * Hkv});
-      if (w == wdec) groups.insert(groups.end(), sc.dec_groups.begin(), sc.dec_groups.end());
+      auto longer = [](const std::pair<int64_t, int64_t>& a, const std::pair<int64_t, int64_t>& b) {
+        return a.first > b.first;
+      };
+      std::sort(groups.begin(), groups.end(), longer);
+      if (w == wdec && !sc.dec_groups.empty()) {  // ascending, the same for every candidate
+        sc.groups3.resize(groups.size() + sc.dec_groups.size());
+        std::merge(groups.begin(), groups.end(), sc.dec_groups.rbegin(), sc.dec_groups.rend(),
+                   sc.groups3.begin(), longer);
+        groups.swap(sc.groups3);
+      }
       const int64_t slots = (int64_t)t.num_cus * (w ? 1 : 2);
-      est += (double)lpt_makespan(groups, slots, sc.load_hist);
+      // past this the estimate exceeds the best so far (which it may equal)
+      const int64_t limit = best >= 0 ? (int64_t)std::floor(best - est) : INT64_MAX;
+      const int64_t span = lpt_makespan(groups, slots, sc.load_hist, limit);
+      if (span > limit) return -1.0;
+      est += (double)span;
     }
     return est;
   };
@@ -602,11 +623,15 @@ void build_plan(const cp_attn_desc& d, const cp_row_meta* rows, int32_t n_rows,
         const int64_t ns = std::max<int64_t>(1, ceil_div(nb, sb));
         for (int64_t s = 0; s < ns; ++s) ++hist[nb * (s + 1) / ns - nb * s / ns];
       });
-      for (int64_t b = 1; b < (int64_t)hist.size(); ++b)
-        if (hist[b] > 0)
-          sc.dec_groups.push_back(
-              {(int64_t)std::ceil((double)(b * B) / std::max(1.0, t.fuse_keys_per_step)) + 1,
-               hist[b] * Hkv});
+      for (int64_t b = 1; b < (int64_t)hist.size(); ++b) {
+        if (hist[b] == 0) continue;
+        const int64_t steps =
+            (int64_t)std::ceil((double)(b * B) / std::max(1.0, t.fuse_keys_per_step)) + 1;
+        if (!sc.dec_groups.empty() && sc.dec_groups.back().first == steps)
+          sc.dec_groups.back().second += hist[b] * Hkv;
+        else
+          sc.dec_groups.push_back({steps, hist[b] * Hkv});
+      }
     }
   }
 

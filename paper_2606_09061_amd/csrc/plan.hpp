@@ -158,7 +158,7 @@ struct PlanScratch {
   std::vector<detail::PrefillItem> items[2];          // 128- and 256-row tiles' key splits
   std::vector<int64_t> candidates;                    // split lengths to score
   std::vector<uint32_t> cut_lim;                      // per tile: last key a split may start at
-  std::vector<std::pair<int64_t, int64_t>> groups2;  // (cost, count) of one split candidate
+  std::vector<std::pair<int64_t, int64_t>> groups2, groups3;  // (cost, count) of one split candidate
   std::vector<std::pair<int64_t, int64_t>> load_hist; // (slot load, slots), by load
   std::vector<PrefillRec> recs_tmp;                   // a record list being re-laid out
   std::vector<int64_t> dec_hist;                      // decode units per block count
