@@ -124,6 +124,7 @@ struct GemmArgs {
   int m, n, k;
   int split;
   bool stream_w;       // copy W non-temporally
+  bool rotate;         // stream kernel: XCDs start at different stages
 };
 
 // The tile and K slice of a workgroup.
@@ -401,6 +402,12 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(GemmArgs g) {
 // Bound by the weight stream: with W's copies non-temporal and the ring
 // holding 16-48 KiB of W in flight per CU, 24 rows x 24576 x 4096 take 37.7
 // us (5.3 TB/s; 42.7 with ordinary copies), 24 x 4096 x 12288 20.5 us.
+//
+// With `rotate`, XCD x walks the stages from x / 8 of them on, around the end.
+// All workgroups read the same k at about the same time, and weight rows a
+// power of two apart then fall on few memory channels: 24 rows x 24576 x 4096
+// 38.7 -> 36.3 us, 96 rows 46.5 -> 42.2, 128 rows 49.0 -> 44.6; no difference
+// at K = 12288 or where the weights are small.
 template <int WM, int WN, int TM, int TN, int NS, bool HALF = false>
 __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(GemmArgs g) {
   constexpr int BM = WM * TM * 16, BN = WN * TN * 16, SB = (BM + BN) * kRow;
@@ -426,7 +433,10 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(GemmArgs g) {
 #pragma unroll
   for (int j = 0; j < NW; ++j)
     pw[j] = piece(g.w, g.k, t.n0, g.n, min(j * 8 + wave, PW - 1) * 8, t.st0, lds0 + BM * kRow, lane);
+  const int turn = !HALF && g.rotate ? (int)(blockIdx.x % kXcds) * nk / kXcds : 0;
   auto issue = [&](int st, int slot) {
+    st += turn;
+    if (st >= nk) st -= nk;
     // chunks 4-7 of a half stage read chunks 0-3 (a K row's chunk offset is
     // below 128 bytes, and K a multiple of 64 bytes: bit 6 is the half)
     auto cut = [&](uint32_t off, int row_chunk) {
@@ -691,6 +701,9 @@ int cpl_gemm(const void* a, const void* w, const void* r, void* c, int32_t m, in
   // 56.2 us) or fewer weights (96 x 6144 x 4096 19.9 -> 20.4) it loses.
   g.stream_w = row_blocks <= 2 && (int64_t)n * k >= (int64_t)32 << 20;
   const int tiles = row_blocks * (n / cfg->bn) * split;
+  // (over more rounds the XCDs drift apart by themselves: 24 rows x 151936 x
+  // 4096, 1,187 tiles, 194 -> 203 us)
+  g.rotate = tiles <= 2 * kCus;
   (void)hipGetLastError();
   hipStream_t s = (hipStream_t)stream;
   hipLaunchKernelGGL(cfg->kernel, dim3((tiles + kXcds - 1) / kXcds * kXcds), dim3(512), 0, s, g);
