@@ -202,11 +202,18 @@ def project_attn(a, w, out, residual=None, stream=None, ws=None):
         raise ValueError(f"projection {M}x{N}x{K}: the kernels need N % 128 == 0 and K % 32 == 0")
 
 
+def _apart(x, y):
+    """Whether two dense tensors share no byte."""
+    px, py = x.data_ptr(), y.data_ptr()
+    return (px + x.numel() * x.element_size() <= py
+            or py + y.numel() * y.element_size() <= px)
+
+
 def _tiled_takes(a, w, out, residual):
     """Whether cpl_gemm can stand in for torch.mm / addmm here: plain dense
     bf16 matrices of matching shapes on the current GPU, 16-byte aligned, that
-    autograd does not follow.  Everything else is left to torch, which
-    computes or refuses it."""
+    autograd does not follow, with no operand under out except a residual that
+    is out.  Everything else is left to torch, which computes or refuses it."""
     import torch
     ts = (a, w, out) if residual is None else (a, w, out, residual)
     for t in ts:
@@ -218,8 +225,10 @@ def _tiled_takes(a, w, out, residual):
     M, K = a.shape
     N = w.shape[0]
     return (M > 0 and w.shape[1] == K and out.shape == (M, N) and N % 128 == 0 and K % 32 == 0
-            and K > 0 and N > 0 and (residual is None or residual.shape == out.shape)
-            and out.data_ptr() not in (a.data_ptr(), w.data_ptr())
+            and K > 0 and N > 0 and _apart(a, out) and _apart(w, out)
+            and (residual is None or (residual.shape == out.shape
+                                      and (residual.data_ptr() == out.data_ptr()
+                                           or _apart(residual, out))))
             and a.device.index == torch.cuda.current_device())
 
 

@@ -101,7 +101,7 @@ def test_bad_arguments_are_rejected():
 
 def test_project_matches_library_and_reference():
     from paper_2606_09061_amd import model as MM
-    for m_rows in (1, 32, 33):          # skinny kernel, then the library GEMM
+    for m_rows in (1, 32, 33):          # skinny kernel, then the tiled one
         a = _bf16((m_rows, 512), 31).to(DEV)
         w = _bf16((256, 512), 32, 0.05).to(DEV)
         x = _bf16((m_rows, 256), 33).to(DEV)
@@ -112,6 +112,56 @@ def test_project_matches_library_and_reference():
         assert err.max() <= 2e-2 * max(1.0, float(np.abs(want).max()))
 
 
+@pytest.mark.parametrize("form", ["dense", "w_strided", "a_strided", "out_at_8_bytes",
+                                  "residual_copy", "residual_overlaps_out", "autograd", "n_odd",
+                                  "side_stream"])
+@pytest.mark.parametrize("rows", [20, 45])
+def test_project_of_every_form(rows, form):
+    """project() on tensors that the tiled kernel takes and on those that stay
+    with the library, against the fp64 product: one bf16 rounding of the
+    result plus fp32 sums (test_gemm_matches_reference's bound); where the
+    library adds a residual after rounding, one more rounding of the product."""
+    from paper_2606_09061_amd import model as MM
+    N, K = (160 if form == "n_odd" else 256), 1024
+    a, w, r = _bf16((rows, K), 61), _bf16((N, K), 62, 0.05), _bf16((rows, N), 63)
+    ad, wd, rd = a.to(DEV), w.to(DEV), None
+    out = torch.empty(rows, N, dtype=torch.bfloat16, device=DEV)
+    stream = None
+    if rows <= 32 and form in ("w_strided", "a_strided", "out_at_8_bytes"):
+        pytest.skip("the skinny kernel's batch sizes: dense and aligned tensors only")
+    if form == "w_strided":
+        wd = torch.zeros(N, K + 64, dtype=torch.bfloat16, device=DEV)[:, :K].copy_(w)
+    elif form == "a_strided":
+        ad = torch.zeros(rows, K + 64, dtype=torch.bfloat16, device=DEV)[:, :K].copy_(a)
+    elif form == "out_at_8_bytes":
+        out = torch.empty(rows * N + 4, dtype=torch.bfloat16, device=DEV)[4:].view(rows, N)
+    elif form == "residual_copy":
+        rd = r.to(DEV)
+    elif form == "residual_overlaps_out":
+        if rows <= 32:
+            pytest.skip("the skinny kernel's batch sizes: residual apart from out, or out itself")
+        buf = torch.empty((rows + 1) * N, dtype=torch.bfloat16, device=DEV)
+        out, rd = buf[:rows * N].view(rows, N), buf[N:].view(rows, N)
+        assert not MM._tiled_takes(ad, wd, out, rd)
+        return
+    elif form == "autograd":
+        wd = torch.nn.Parameter(wd)
+        with pytest.raises(RuntimeError) if rows > 32 else torch.no_grad():
+            MM.project(ad, wd, out)
+        if rows > 32:
+            return
+    elif form == "side_stream":
+        stream = torch.cuda.Stream(DEV)
+        stream.wait_stream(torch.cuda.current_stream(DEV))
+    MM.project(ad, wd, out, rd, stream.cuda_stream if stream is not None else None)
+    torch.cuda.synchronize()
+    prod = _f64(a) @ _f64(w).T
+    want = prod + (_f64(r) if rd is not None else 0.0)
+    slack = 2.0 ** -20 * (np.abs(_f64(a)) @ np.abs(_f64(w)).T) + 2.0 ** -8 * np.abs(prod)
+    err = np.abs(_f64(out) - want)
+    assert np.all(err <= 2.0 ** -8 * np.abs(want) + slack + 1e-6), f"max err {err.max():.3e}"
+
+
 def _small_model():
     cfg = M.ModelConfig(hidden=256, layers=1, hq=4, hkv=2, head_dim=64, inter=512, vocab=1000,
                         theta=1e4)
@@ -119,8 +169,8 @@ def _small_model():
 
 
 @pytest.mark.parametrize("rows", [
-    [[1, 40, 1, 41], [0, 0, 70, 70], [2, 100, 33, 133], [3, 0, 1, 1]],   # 105 tokens: library GEMMs
-    [[1, 40, 1, 41], [0, 0, 20, 20], [2, 100, 5, 105], [3, 0, 1, 1]],    # 27 tokens: skinny kernel
+    [[1, 40, 1, 41], [0, 0, 70, 70], [2, 100, 33, 133], [3, 0, 1, 1]],   # 105 tokens: tiled GEMMs
+    [[1, 40, 1, 41], [0, 0, 20, 20], [2, 100, 5, 105], [3, 0, 1, 1]],    # 27 tokens: skinny and tiled
 ])
 def test_decoder_layer_matches_reference(rows):
     m = _small_model()
