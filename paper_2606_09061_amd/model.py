@@ -124,13 +124,18 @@ def skinny_faster(m, n, k):
 # 4096) 31.3 / 36.5, 33.4 / 37.3, 37.9 / 38.0, 42.3 / 39.5.  Long rows (K > N:
 # the down projection) need more workgroups than their column slices give,
 # which the tiled kernel's split over K has: 4096 x 12288 21.1 / 19.3 at 8
-# rows, 21.9 / 19.8 at 16, 31.3 / 21.0 at 32; 2048 x 6144 10.8 / 9.2 at 8
-# (20.4 / 19.7 at 1 row, where its second launch costs as much on the host).
-# Wide projections stream their activations again for every slice and lose
-# from 17 rows (LM head, 151936 x 4096: 196.7 / 192.1 at 16, 209.2 / 193.8 at
-# 20).  The tiled kernel takes N % 128 == 0 only.
-def _skinny_over_tiled(m, n, k):
-    return n % 128 != 0 or m < 8 or (k <= n and (m <= 16 or (m <= 24 and n < 8192)))
+# rows, 21.9 / 19.8 at 16, 31.3 / 21.0 at 32.  Wide projections stream their
+# activations again for every slice and lose from 17 rows (LM head, 151936 x
+# 4096: 196.7 / 192.1 at 16, 209.2 / 193.8 at 20).  Below 32 M weights a step
+# of the layer waits for the host, and the split's second launch and scratch
+# cost more than the kernel gains (down 2048 x 6144 10.8 / 9.2 at 8 rows, but
+# its feed-forward block 31 / 45 us; the projections around the step at hidden
+# 4,096, 32 rows, 34.3 / 37.7).  The tiled kernel takes N % 128 == 0 only.
+def _skinny_fastest(m, n, k):
+    if m > 32 or n % 32 or k % 256 or m < 1:
+        return False
+    return (m < 8 or n * k < 32 << 20 or n % 128 != 0
+            or (k <= n and (m <= 16 or (m <= 24 and n < 8192))))
 
 
 def gemm_skinny(a, w, out, residual=None, stream=None):
@@ -155,11 +160,13 @@ def _scratch(nbytes, device, stream):
     allocator hands them out again only behind those kernels; None when there
     are none to be had."""
     import torch
-    if isinstance(stream, int):
-        stream = (torch.cuda.ExternalStream(stream, device=device) if stream
-                  else torch.cuda.default_stream(device))
     try:
-        with torch.cuda.stream(stream):   # None: the current stream
+        if stream is None:   # the current stream, torch's own choice
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        if isinstance(stream, int):
+            stream = (torch.cuda.ExternalStream(stream, device=device) if stream
+                      else torch.cuda.default_stream(device))
+        with torch.cuda.stream(stream):
             return torch.empty(nbytes, dtype=torch.uint8, device=device)
     except torch.cuda.OutOfMemoryError:
         return None
@@ -194,7 +201,8 @@ def project_attn(a, w, out, residual=None, stream=None, ws=None):
     tiled MFMA GEMM above (``ws``: its split-K workspace, see gemm)."""
     M, K = a.shape
     N = w.shape[0]
-    if skinny_faster(M, N, K) and (_skinny_over_tiled(M, N, K) or not _aligned(out, residual)):
+    if _skinny_fastest(M, N, K) or (M <= 32 and skinny_faster(M, N, K)
+                                    and not _aligned(out, residual)):
         gemm_skinny(a, w, out, residual, stream)
     elif N % 128 == 0 and K % 32 == 0:
         gemm(a, w, out, residual, stream, ws)
@@ -203,10 +211,9 @@ def project_attn(a, w, out, residual=None, stream=None, ws=None):
 
 
 def _apart(x, y):
-    """Whether two dense tensors share no byte."""
+    """Whether two dense bf16 tensors share no byte."""
     px, py = x.data_ptr(), y.data_ptr()
-    return (px + x.numel() * x.element_size() <= py
-            or py + y.numel() * y.element_size() <= px)
+    return px + 2 * x.numel() <= py or py + 2 * y.numel() <= px
 
 
 def _tiled_takes(a, w, out, residual):
@@ -215,21 +222,21 @@ def _tiled_takes(a, w, out, residual):
     autograd does not follow, with no operand under out except a residual that
     is out.  Everything else is left to torch, which computes or refuses it."""
     import torch
-    ts = (a, w, out) if residual is None else (a, w, out, residual)
-    for t in ts:
+    dev = torch.cuda.current_device()
+    for t in (a, w, out) if residual is None else (a, w, out, residual):
         if (type(t) not in (torch.Tensor, torch.nn.Parameter) or t.dtype != torch.bfloat16
-                or t.dim() != 2 or not t.is_cuda or t.device != a.device
+                or t.dim() != 2 or t.get_device() != dev or not t.is_cuda
                 or not t.is_contiguous() or t.data_ptr() % 16
                 or (t.requires_grad and torch.is_grad_enabled())):
             return False
     M, K = a.shape
     N = w.shape[0]
-    return (M > 0 and w.shape[1] == K and out.shape == (M, N) and N % 128 == 0 and K % 32 == 0
-            and K > 0 and N > 0 and _apart(a, out) and _apart(w, out)
-            and (residual is None or (residual.shape == out.shape
-                                      and (residual.data_ptr() == out.data_ptr()
-                                           or _apart(residual, out))))
-            and a.device.index == torch.cuda.current_device())
+    if (M == 0 or K == 0 or N == 0 or N % 128 or K % 32 or w.shape[1] != K
+            or out.shape != (M, N) or not _apart(a, out) or not _apart(w, out)):
+        return False
+    return residual is None or (residual.shape == out.shape
+                                and (residual.data_ptr() == out.data_ptr()
+                                     or _apart(residual, out)))
 
 
 def project(a, w, out, residual=None, stream=None, ws=None):
@@ -244,12 +251,11 @@ def project(a, w, out, residual=None, stream=None, ws=None):
     import torch
     M, K = a.shape
     N = w.shape[0]
-    skinny = skinny_faster(M, N, K)
-    if skinny and _skinny_over_tiled(M, N, K):
+    if _skinny_fastest(M, N, K):
         gemm_skinny(a, w, out, residual, stream)
     elif _tiled_takes(a, w, out, residual):
         gemm(a, w, out, residual, stream, ws)
-    elif skinny:
+    elif skinny_faster(M, N, K):
         gemm_skinny(a, w, out, residual, stream)
     elif residual is None:
         torch.mm(a, w.t(), out=out)
