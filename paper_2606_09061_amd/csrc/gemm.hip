@@ -73,6 +73,15 @@ __device__ __forceinline__ void copy16_to_lds(const char* base, uint32_t off, ui
                  : "memory");
 #endif
 }
+// The same with a 64-bit address per lane.
+__device__ __forceinline__ void copy16_to_lds_far(const char* src, uint32_t dst, bool stream) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  if (stream)
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(src), "{m0}"(dst) : "memory");
+  else
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(dst) : "memory");
+#endif
+}
 
 // s_waitcnt with vmcnt <= N, the other counters unconstrained (gfx9 encoding)
 template <int N>
@@ -156,19 +165,31 @@ __device__ __forceinline__ bool pick_tile(const GemmArgs& g, Tile& t) {
 
 // One 1 KiB piece of a staged tile: 8 rows of `src` [limit][K] from `row` (rows past the
 // last read the last: their products are discarded).
-struct Piece {
-  const char* base;  // wave-uniform
-  uint32_t off;      // this lane's byte offset from it (7 rows of K at most)
-  uint32_t dst;      // LDS address in slot 0
+// FAR: K rows so long that 7 of them pass 32 bits.
+template <bool FAR>
+struct Offset {
+  typedef uint32_t type;
 };
-__device__ __forceinline__ Piece piece(const uint16_t* src, int k, int row0, int limit, int row,
-                                       int st0, uint32_t lds, int lane) {
+template <>
+struct Offset<true> {
+  typedef uint64_t type;
+};
+template <bool FAR>
+struct Piece {
+  const char* base;                  // wave-uniform
+  typename Offset<FAR>::type off;    // this lane's byte offset from it (7 rows of K at most)
+  uint32_t dst;                      // LDS address in slot 0
+};
+template <bool FAR = false>
+__device__ __forceinline__ Piece<FAR> piece(const uint16_t* src, int k, int row0, int limit, int row,
+                                            int st0, uint32_t lds, int lane) {
+  typedef typename Offset<FAR>::type offset_t;
   const int rr = row + (lane >> 3);
   const int first = min(row0 + row, limit - 1);
   const int chunk = (lane & 7) ^ ((rr >> 1) & 7);
-  Piece p;
+  Piece<FAR> p;
   p.base = reinterpret_cast<const char*>(src + (int64_t)first * k + (int64_t)st0 * kStageK);
-  p.off = (uint32_t)(min(row0 + rr, limit - 1) - first) * (uint32_t)k * 2 + (uint32_t)chunk * 16;
+  p.off = (offset_t)(min(row0 + rr, limit - 1) - first) * (offset_t)k * 2 + (offset_t)chunk * 16;
   p.dst = lds + row * kRow;
   return p;
 }
@@ -288,7 +309,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(GemmArgs g) {
 
   // the group's A pieces, the T0 parts first, dealt in turn to its 4 waves;
   // W's to all 8 (where they do not divide, the last piece is copied twice)
-  Piece pa[NA], pw[NW];
+  Piece<false> pa[NA], pw[NW];
 #pragma unroll
   for (int j = 0; j < NA; ++j) {
     const int x = min(j * 4 + (wave & 3), GP - 1);
@@ -408,7 +429,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(GemmArgs g) {
 // power of two apart then fall on few memory channels: 24 rows x 24576 x 4096
 // 38.7 -> 36.3 us, 96 rows 46.5 -> 42.2, 128 rows 49.0 -> 44.6; no difference
 // at K = 12288 or where the weights are small.
-template <int WM, int WN, int TM, int TN, int NS, bool HALF = false>
+template <int WM, int WN, int TM, int TN, int NS, bool HALF = false, bool FAR = false>
 __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(GemmArgs g) {
   constexpr int BM = WM * TM * 16, BN = WN * TN * 16, SB = (BM + BN) * kRow;
   constexpr int PA = BM / 8, PW = BN / 8, NA = (PA + 7) / 8, NW = (PW + 7) / 8, L = NA + NW;
@@ -424,36 +445,33 @@ __global__ __launch_bounds__(512, 2) void gemm_stream_kernel(GemmArgs g) {
   const bool stream = g.stream_w;
   const int nk = t.nk;
   // the slice's last stage when it holds only 32 k, else past the end
-  const int half = HALF && t.st0 + nk == (g.k + kStageK - 1) / kStageK ? nk - 1 : nk;
+  const int half = HALF && g.k % kStageK && t.st0 + nk == (g.k + kStageK - 1) / kStageK ? nk - 1 : nk;
 
-  Piece pa[NA], pw[NW];
+  Piece<FAR> pa[NA], pw[NW];
 #pragma unroll
   for (int j = 0; j < NA; ++j)
-    pa[j] = piece(g.a, g.k, t.m0, g.m, min(j * 8 + wave, PA - 1) * 8, t.st0, lds0, lane);
+    pa[j] = piece<FAR>(g.a, g.k, t.m0, g.m, min(j * 8 + wave, PA - 1) * 8, t.st0, lds0, lane);
 #pragma unroll
   for (int j = 0; j < NW; ++j)
-    pw[j] = piece(g.w, g.k, t.n0, g.n, min(j * 8 + wave, PW - 1) * 8, t.st0, lds0 + BM * kRow, lane);
+    pw[j] = piece<FAR>(g.w, g.k, t.n0, g.n, min(j * 8 + wave, PW - 1) * 8, t.st0, lds0 + BM * kRow, lane);
   const int turn = !HALF && g.rotate ? (int)(blockIdx.x % kXcds) * nk / kXcds : 0;
   auto issue = [&](int st, int slot) {
     st += turn;
     if (st >= nk) st -= nk;
     // chunks 4-7 of a half stage read chunks 0-3 (a K row's chunk offset is
     // below 128 bytes, and K a multiple of 64 bytes: bit 6 is the half)
-    auto cut = [&](uint32_t off, int row_chunk) {
-      return HALF && st == half && row_chunk >= 4 ? off - 64 : off;
+    auto copy = [&](const Piece<FAR>& p, int row, bool nt) {
+      const int chunk = (lane & 7) ^ ((row >> 1) & 7);
+      const auto off = HALF && st == half && chunk >= 4 ? p.off - 64 : p.off;
+      if constexpr (FAR)
+        copy16_to_lds_far(p.base + (int64_t)st * kRow + off, p.dst + slot * SB, nt);
+      else
+        copy16_to_lds(p.base + (int64_t)st * kRow, off, p.dst + slot * SB, nt);
     };
 #pragma unroll
-    for (int j = 0; j < NW; ++j) {
-      const int row = min(j * 8 + wave, PW - 1) * 8 + (lane >> 3);
-      copy16_to_lds(pw[j].base + (int64_t)st * kRow, cut(pw[j].off, (lane & 7) ^ ((row >> 1) & 7)),
-                    pw[j].dst + slot * SB, stream);
-    }
+    for (int j = 0; j < NW; ++j) copy(pw[j], min(j * 8 + wave, PW - 1) * 8 + (lane >> 3), stream);
 #pragma unroll
-    for (int j = 0; j < NA; ++j) {
-      const int row = min(j * 8 + wave, PA - 1) * 8 + (lane >> 3);
-      copy16_to_lds(pa[j].base + (int64_t)st * kRow, cut(pa[j].off, (lane & 7) ^ ((row >> 1) & 7)),
-                    pa[j].dst + slot * SB, false);
-    }
+    for (int j = 0; j < NA; ++j) copy(pa[j], min(j * 8 + wave, PA - 1) * 8 + (lane >> 3), false);
   };
 
   const uint32_t ofs[2] = {operand_offset(0, lane), operand_offset(1, lane)};
@@ -566,10 +584,10 @@ template <int WM, int WN, int TM, int TN, int NS>
 constexpr Cfg tile_cfg(float stage_us, float tile_us) {
   return {WM * TM * 16, WN * TN * 16, stage_us, tile_us, gemm_tile_kernel<WM, WN, TM, TN, NS>};
 }
-template <int WM, int WN, int TM, int TN, int NS, bool HALF = false>
+template <int WM, int WN, int TM, int TN, int NS, bool HALF = false, bool FAR = false>
 constexpr Cfg stream_cfg(float stage_us, float tile_us) {
   return {WM * TM * 16, WN * TN * 16, stage_us, tile_us,
-          gemm_stream_kernel<WM, WN, TM, TN, NS, HALF>};
+          gemm_stream_kernel<WM, WN, TM, TN, NS, HALF, FAR>};
 }
 
 // Tile configurations (CPL_GEMM_CFG selects one by its index), each with the
@@ -600,6 +618,9 @@ constexpr int kDefaultCfg = 8;  // divides every N
 // for K an odd number of 32s
 constexpr Cfg kHalf64 = stream_cfg<2, 4, 2, 2, 3, true>(0.f, 0.f);
 constexpr Cfg kHalf128 = stream_cfg<2, 4, 4, 2, 4, true>(0.f, 0.f);
+// for any K, of which 7 rows and a row's chunk may pass 32 bits of byte offset
+constexpr int kMaxNearK = (int)((0xffffffffu - kRow) / 14);
+constexpr Cfg kFar = stream_cfg<2, 4, 2, 2, 3, true, true>(0.f, 0.f);
 
 int env_int(const char* name, int dflt) {
   const char* s = getenv(name);
@@ -657,6 +678,7 @@ void choose(int M, int N, int K, size_t ws_floats, const Cfg** cfg, int* split) 
   }
   if (!best) best = &kCfgs[kDefaultCfg];
   if (half) best = M <= 64 ? &kHalf64 : &kHalf128;
+  if (K > kMaxNearK) best = &kFar;
   *cfg = best;
   *split = best_split;
 }

@@ -339,6 +339,28 @@ def test_gemm_every_tile_matches_reference(monkeypatch, cfg, M, N, K, split):
     assert np.all(err <= 2.0 ** -8 * np.abs(want) + slack + 1e-6), f"max err {err.max():.3e}"
 
 
+def _zeros_or_skip(*shape):
+    if torch.cuda.mem_get_info(DEV)[0] < 1.1 * 2 * math.prod(shape):
+        pytest.skip("not enough free GPU memory")
+    return torch.zeros(*shape, dtype=torch.bfloat16, device=DEV)
+
+
+@pytest.mark.parametrize("K", [306783392, 306783424])
+def test_gemm_of_rows_beyond_32_bits(K):
+    """Eight rows of this many k (a whole and a half last stage) span more than
+    4 GiB, the reach of a 32-bit offset from the first of them.  A few columns
+    of the operands are not zero, so that the fp64 product is small."""
+    print(f"gemm of long rows K={K}", flush=True)
+    a, w = _zeros_or_skip(9, K), _zeros_or_skip(128, K)
+    cols = torch.tensor([0, 1, 63, 64, 1000003, K // 2, K - 65, K - 33, K - 32, K - 1], device=DEV)
+    av, wv = _bf16((9, 10), 71), _bf16((128, 10), 72)
+    a[:, cols], w[:, cols] = av.to(DEV), wv.to(DEV)
+    out = torch.full((9, 128), float("nan"), dtype=torch.bfloat16, device=DEV)
+    M.gemm(a, w, out)
+    torch.cuda.synchronize()
+    _close(_f64(out), _f64(av) @ _f64(wv).T, abs_=1e-4)
+
+
 def test_gemm_rejects_unsupported_shapes():
     lib = M.load()
     x = torch.zeros(512, 512, dtype=torch.bfloat16, device=DEV)
