@@ -53,6 +53,7 @@ constexpr int kStageK = 64;              // k per stage
 constexpr int kRow = kStageK * 2;        // bytes of a staged row
 constexpr int kMaxLds = 160 * 1024;
 constexpr int kMaxSplit = 8;
+constexpr int kGridX = 1 << 20;          // workgroups in a row of the grid
 
 __device__ __forceinline__ f32x4_t mfma(uint4 a, uint4 b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
@@ -148,8 +149,9 @@ template <int BM, int BN>
 __device__ __forceinline__ bool pick_tile(const GemmArgs& g, Tile& t) {
   const int mb = (g.m + BM - 1) / BM, nb = g.n / BN, tiles = mb * nb * g.split;
   const int per = (tiles + kXcds - 1) / kXcds;
-  int i = (int)(blockIdx.x % kXcds) * per + (int)(blockIdx.x / kXcds);
-  if (i >= tiles || (int)(blockIdx.x / kXcds) >= per) return false;
+  const unsigned wg = blockIdx.y * gridDim.x + blockIdx.x;  // (gridDim.x: a multiple of the XCDs)
+  int i = (int)(wg % kXcds) * per + (int)(wg / kXcds);
+  if (i >= tiles || (int)(wg / kXcds) >= per) return false;
   t.slice = i / (mb * nb);
   i -= t.slice * mb * nb;
   const int group = i / (kRowGroup * nb);
@@ -728,7 +730,9 @@ int cpl_gemm(const void* a, const void* w, const void* r, void* c, int32_t m, in
   g.rotate = tiles <= 2 * kCus;
   (void)hipGetLastError();
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(cfg->kernel, dim3((tiles + kXcds - 1) / kXcds * kXcds), dim3(512), 0, s, g);
+  // a launch takes fewer than 2^32 threads in x: larger grids are laid out in rows
+  const int wgs = (tiles + kXcds - 1) / kXcds * kXcds, grid_x = wgs < kGridX ? wgs : kGridX;
+  hipLaunchKernelGGL(cfg->kernel, dim3(grid_x, (wgs + grid_x - 1) / grid_x), dim3(512), 0, s, g);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && split > 1) {
     launch_sum<kMaxSplit>(g, s);

@@ -361,6 +361,24 @@ def test_gemm_of_rows_beyond_32_bits(K):
     _close(_f64(out), _f64(av) @ _f64(wv).T, abs_=1e-4)
 
 
+def test_gemm_of_more_columns_than_a_grid_row_holds():
+    """2^30 + 128 columns are more workgroups than one row of a launch's grid
+    takes.  A few rows of the weights are not zero."""
+    N, K = (1 << 30) + 128, 32
+    print(f"gemm of many columns N={N}", flush=True)
+    w, out = _zeros_or_skip(N, K), _zeros_or_skip(1, N)
+    rows = torch.tensor([0, 127, 128, 1 << 20, (1 << 27) - 1, 1 << 27, 1 << 29, N - 129, N - 1],
+                        device=DEV)
+    a, wv = _bf16((1, K), 73), _bf16((9, K), 74)
+    w[rows] = wv.to(DEV)
+    out.fill_(float("nan"))
+    M.gemm(a.to(DEV), w, out)
+    torch.cuda.synchronize()
+    _close(_f64(out[:, rows]), _f64(a) @ _f64(wv).T, abs_=1e-4)
+    out[:, rows] = 0
+    assert int(torch.count_nonzero(out)) == 0
+
+
 def test_gemm_rejects_unsupported_shapes():
     lib = M.load()
     x = torch.zeros(512, 512, dtype=torch.bfloat16, device=DEV)
