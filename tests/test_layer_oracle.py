@@ -5,6 +5,7 @@ import math
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import layer as ref
 
@@ -131,6 +132,23 @@ def test_skinny_dispatch_follows_measured_table():
         assert not skinny_faster(33, n, k) and not skinny_faster(128, n, k)
     assert skinny_faster(32, *qkv) and skinny_faster(32, *gate_up) and skinny_faster(32, *down)
     assert not skinny_faster(1, 1000, 256) and not skinny_faster(1, 64, 320)   # unsupported shapes
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_project_of_cpu_tensors(dtype):
+    """Above the skinny kernel's batch sizes project() leaves tensors in host
+    memory to torch, also where there is no GPU."""
+    from paper_2606_09061_amd import model as M
+    g = torch.Generator().manual_seed(3)
+    a, w, x = (torch.randn(*s, generator=g).to(dtype) for s in ((45, 256), (128, 256), (45, 128)))
+    out = torch.empty(45, 128, dtype=dtype)
+    M.project(a, w, out)
+    assert torch.equal(out, torch.mm(a, w.t()))
+    M.project(a, w, out, x)
+    assert torch.equal(out, torch.addmm(x, a, w.t()))
+    want = torch.addmm(x, a, w.t())
+    M.project(a, w, x, x)
+    assert torch.equal(x, want)
 
 
 def test_gemm_validates_before_launching():
