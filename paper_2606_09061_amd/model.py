@@ -219,10 +219,11 @@ def _apart(x, y):
 def _tiled_takes(a, w, out, residual):
     """Whether cpl_gemm can stand in for torch.mm / addmm here: plain dense
     bf16 matrices of matching shapes on the current GPU, 16-byte aligned, that
-    autograd does not follow, with no operand under out except a residual that
-    is out.  Everything else is left to torch, which computes or refuses it."""
+    autograd does not follow (backward, or forward: inside a dual level), with
+    no operand under out except a residual that is out.  Everything else is
+    left to torch, which computes or refuses it."""
     import torch
-    if not a.is_cuda:
+    if not a.is_cuda or torch.autograd.forward_ad._current_level >= 0:
         return False
     dev = torch.cuda.current_device()
     for t in (a, w, out) if residual is None else (a, w, out, residual):

@@ -162,6 +162,29 @@ def test_project_of_every_form(rows, form):
     assert np.all(err <= 2.0 ** -8 * np.abs(want) + slack + 1e-6), f"max err {err.max():.3e}"
 
 
+def _torch_operands(rows=45):
+    """a [rows, 1024], w [256, 1024] and a result's place, of the tiled kernel's kind."""
+    return (_bf16((rows, 1024), 64).to(DEV), _bf16((256, 1024), 65, 0.05).to(DEV),
+            _bf16((rows, 256), 66).to(DEV))
+
+
+def test_project_in_forward_mode():
+    """Inside a dual level the products above the skinny kernel's batch sizes
+    are torch's: refused into a given tensor, with their tangent in place."""
+    import torch.autograd.forward_ad as fwd
+    from paper_2606_09061_amd import model as MM
+    a, w, x = _torch_operands()
+    tangent = torch.randn_like(a)
+    with fwd.dual_level():
+        dual = fwd.make_dual(a, tangent)
+        with pytest.raises(NotImplementedError):
+            MM.project(dual, w, torch.empty_like(x))
+        y = x.clone()
+        MM.project(dual, w, y, y)
+        got = fwd.unpack_dual(y).tangent
+        assert got is not None and torch.equal(got, torch.mm(tangent, w.t()))
+
+
 def _small_model():
     cfg = M.ModelConfig(hidden=256, layers=1, hq=4, hkv=2, head_dim=64, inter=512, vocab=1000,
                         theta=1e4)
