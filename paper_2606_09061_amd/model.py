@@ -219,11 +219,12 @@ def _apart(x, y):
 def _tiled_takes(a, w, out, residual):
     """Whether cpl_gemm can stand in for torch.mm / addmm here: plain dense
     bf16 matrices of matching shapes on the current GPU, 16-byte aligned, that
-    autograd does not follow (backward, or forward: inside a dual level), with
-    no operand under out except a residual that is out.  Everything else is
-    left to torch, which computes or refuses it."""
+    autograd does not follow (backward, or forward: inside a dual level) and no
+    function transform wraps, with no operand under out except a residual that
+    is out.  Everything else is left to torch, which computes or refuses it."""
     import torch
-    if not a.is_cuda or torch.autograd.forward_ad._current_level >= 0:
+    if (not a.is_cuda or torch.autograd.forward_ad._current_level >= 0
+            or torch._C._are_functorch_transforms_active()):
         return False
     dev = torch.cuda.current_device()
     for t in (a, w, out) if residual is None else (a, w, out, residual):

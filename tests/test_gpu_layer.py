@@ -185,6 +185,30 @@ def test_project_in_forward_mode():
         assert got is not None and torch.equal(got, torch.mm(tangent, w.t()))
 
 
+@pytest.mark.parametrize("transform", ["vmap", "jvp", "grad", "functionalize"])
+def test_project_in_function_transforms(transform):
+    """The wrapped tensors of torch.func have no memory of their own; the
+    product above the skinny kernel's batch sizes follows them as torch's."""
+    from paper_2606_09061_amd import model as MM
+    a, w, x = _torch_operands()
+
+    def f(t, product):
+        y = x + 0 * t[:, :256]          # wrapped like t
+        product(t, y)
+        return y
+
+    def ours(t):
+        return f(t, lambda u, y: MM.project(u, w, y, y))
+
+    def torchs(t):
+        return f(t, lambda u, y: y.addmm_(u, w.t()))
+    run = {"vmap": lambda g: torch.func.vmap(g)(torch.stack([a, 2 * a])),
+           "jvp": lambda g: torch.stack(torch.func.jvp(g, (a,), (torch.ones_like(a),))),
+           "grad": lambda g: torch.func.grad(lambda t: g(t).float().sum())(a),
+           "functionalize": lambda g: torch.func.functionalize(g)(a)}[transform]
+    assert torch.equal(run(ours), run(torchs))
+
+
 def _small_model():
     cfg = M.ModelConfig(hidden=256, layers=1, hq=4, hkv=2, head_dim=64, inter=512, vocab=1000,
                         theta=1e4)
