@@ -216,14 +216,33 @@ def _apart(x, y):
     return px + 2 * x.numel() <= py or py + 2 * y.numel() <= px
 
 
+def _function_mode():
+    """Whether a torch function mode other than a default device's is active."""
+    import torch
+    from torch.utils._device import DeviceContext
+    return any(type(torch._C._get_function_stack_at(i)) is not DeviceContext
+               for i in range(torch._C._len_torch_function_stack()))
+
+
+def _watched():
+    """Whether torch has to see the operations of this call: under the compiler,
+    in a trace, inside a dispatch or function mode (flop counters, tracers; the
+    mode of a default device concerns only factories)."""
+    import torch
+    return (torch.compiler.is_compiling() or torch._C._get_tracing_state() is not None
+            or torch._C._len_torch_dispatch_stack() > 0
+            or (torch._C._len_torch_function_stack() > 0 and _function_mode()))
+
+
 def _tiled_takes(a, w, out, residual):
     """Whether cpl_gemm can stand in for torch.mm / addmm here: plain dense
     bf16 matrices of matching shapes on the current GPU, 16-byte aligned, that
     autograd does not follow (backward, or forward: inside a dual level) and no
     function transform wraps, with no operand under out except a residual that
-    is out.  Everything else is left to torch, which computes or refuses it."""
+    is out, and nobody watching.  Everything else is left to torch, which
+    computes or refuses it."""
     import torch
-    if (not a.is_cuda or torch.autograd.forward_ad._current_level >= 0
+    if (_watched() or not a.is_cuda or torch.autograd.forward_ad._current_level >= 0
             or torch._C._are_functorch_transforms_active()):
         return False
     dev = torch.cuda.current_device()

@@ -209,6 +209,41 @@ def test_project_in_function_transforms(transform):
     assert torch.equal(run(ours), run(torchs))
 
 
+def test_project_under_modes_traces_and_the_compiler():
+    """Whoever watches torch's operations sees the products above the skinny
+    kernel's batch sizes; the mode of a default device watches nothing."""
+    from torch.utils.flop_counter import FlopCounterMode
+    from paper_2606_09061_amd import model as MM
+    a, w, x = _torch_operands()
+    want = torch.empty_like(x)
+    torch.mm(a, w.t(), out=want)
+
+    def ours(t):
+        out = torch.empty_like(x)
+        MM.project(t, w, out)
+        return out
+    with FlopCounterMode(display=False) as counter:
+        ours(a)
+    assert counter.get_total_flops() == 2 * 45 * 256 * 1024
+    from torch.overrides import TorchFunctionMode
+
+    class Seen(TorchFunctionMode):
+        names = []
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            self.names.append(getattr(func, "__name__", ""))
+            return func(*args, **(kwargs or {}))
+    with Seen():
+        ours(a)
+    assert "mm" in Seen.names
+    traced = torch.jit.trace(ours, (a,), check_trace=False)
+    assert torch.equal(traced(2 * a), 2 * want)
+    compiled = torch.compile(ours, backend="eager", fullgraph=True)
+    assert torch.equal(compiled(a), want)
+    with torch.device(DEV):
+        assert MM._tiled_takes(a, w, x, None)
+
+
 def _small_model():
     cfg = M.ModelConfig(hidden=256, layers=1, hq=4, hkv=2, head_dim=64, inter=512, vocab=1000,
                         theta=1e4)
