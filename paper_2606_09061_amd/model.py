@@ -243,7 +243,8 @@ def _tiled_takes(a, w, out, residual):
     computes or refuses it."""
     import torch
     if (_watched() or not a.is_cuda or torch.autograd.forward_ad._current_level >= 0
-            or torch._C._are_functorch_transforms_active()):
+            or torch._C._are_functorch_transforms_active()
+            or (out.is_inference() and not torch.is_inference_mode_enabled())):
         return False
     dev = torch.cuda.current_device()
     for t in (a, w, out) if residual is None else (a, w, out, residual):
@@ -277,6 +278,8 @@ def project(a, w, out, residual=None, stream=None, ws=None):
         gemm_skinny(a, w, out, residual, stream)
     elif _tiled_takes(a, w, out, residual):
         gemm(a, w, out, residual, stream, ws)
+        if not skinny_faster(M, N, K) and not out.is_inference():
+            torch.autograd.graph.increment_version(out)   # as torch's product does
     elif skinny_faster(M, N, K):
         gemm_skinny(a, w, out, residual, stream)
     elif residual is None:

@@ -244,6 +244,30 @@ def test_project_under_modes_traces_and_the_compiler():
         assert MM._tiled_takes(a, w, x, None)
 
 
+def test_project_tells_autograd_that_out_changed():
+    """A tensor that autograd saved and project() then overwrote is noticed, and
+    inference tensors are written in inference mode only, as by torch's product
+    (above the skinny kernel's batch sizes)."""
+    from paper_2606_09061_amd import model as MM
+    a, w, x = _torch_operands()
+    leaf = torch.ones(45, 256, device=DEV, requires_grad=True)
+    loss = (leaf * x).sum()             # saves x
+    before = x._version
+    MM.project(a, w, x)
+    assert x._version == before + 1
+    with pytest.raises(RuntimeError, match="modified by an inplace operation"):
+        loss.backward()
+    with torch.inference_mode():
+        y = torch.empty(45, 256, dtype=torch.bfloat16, device=DEV)
+        MM.project(a, w, y)
+        assert torch.equal(y, x)
+        before = x._version
+        MM.project(a, w, x)
+    assert x._version == before + 1
+    with pytest.raises(RuntimeError, match="inference"):
+        MM.project(a, w, y)
+
+
 def _small_model():
     cfg = M.ModelConfig(hidden=256, layers=1, hq=4, hkv=2, head_dim=64, inter=512, vocab=1000,
                         theta=1e4)
