@@ -249,7 +249,8 @@ def _tiled_takes(a, w, out, residual):
     dev = torch.cuda.current_device()
     for t in (a, w, out) if residual is None else (a, w, out, residual):
         if (type(t) not in (torch.Tensor, torch.nn.Parameter) or t.dtype != torch.bfloat16
-                or t.dim() != 2 or t.get_device() != dev or not t.is_contiguous() or t.data_ptr() % 16
+                or t.dim() != 2 or t.get_device() != dev or not t.is_contiguous()
+                or t.is_neg() or t.data_ptr() % 16
                 or (t.requires_grad and torch.is_grad_enabled())):
             return False
     M, K = a.shape

@@ -112,7 +112,7 @@ def test_project_matches_library_and_reference():
         assert err.max() <= 2e-2 * max(1.0, float(np.abs(want).max()))
 
 
-@pytest.mark.parametrize("form", ["dense", "w_strided", "a_strided", "out_at_8_bytes",
+@pytest.mark.parametrize("form", ["dense", "w_strided", "a_strided", "a_negated", "out_at_8_bytes",
                                   "residual_copy", "residual_overlaps_out", "autograd", "n_odd",
                                   "side_stream"])
 @pytest.mark.parametrize("rows", [20, 45])
@@ -127,12 +127,14 @@ def test_project_of_every_form(rows, form):
     ad, wd, rd = a.to(DEV), w.to(DEV), None
     out = torch.empty(rows, N, dtype=torch.bfloat16, device=DEV)
     stream = None
-    if rows <= 32 and form in ("w_strided", "a_strided", "out_at_8_bytes"):
-        pytest.skip("the skinny kernel's batch sizes: dense and aligned tensors only")
+    if rows <= 32 and form in ("w_strided", "a_strided", "a_negated", "out_at_8_bytes"):
+        pytest.skip("the skinny kernel's batch sizes: dense, plain and aligned tensors only")
     if form == "w_strided":
         wd = torch.zeros(N, K + 64, dtype=torch.bfloat16, device=DEV)[:, :K].copy_(w)
     elif form == "a_strided":
         ad = torch.zeros(rows, K + 64, dtype=torch.bfloat16, device=DEV)[:, :K].copy_(a)
+    elif form == "a_negated":       # the sign is in the view, not in memory
+        ad = torch._neg_view(-ad)
     elif form == "out_at_8_bytes":
         out = torch.empty(rows * N + 4, dtype=torch.bfloat16, device=DEV)[4:].view(rows, N)
     elif form == "residual_copy":
