@@ -202,7 +202,7 @@ def project_attn(a, w, out, residual=None, stream=None, ws=None):
     M, K = a.shape
     N = w.shape[0]
     if _skinny_fastest(M, N, K) or (M <= 32 and skinny_faster(M, N, K)
-                                    and not _aligned(out, residual)):
+                                    and not _aligned(out, residual, ws)):
         gemm_skinny(a, w, out, residual, stream)
     elif N % 128 == 0 and K % 32 == 0:
         gemm(a, w, out, residual, stream, ws)

@@ -270,6 +270,19 @@ def test_project_tells_autograd_that_out_changed():
         MM.project(a, w, y)
 
 
+def test_project_attn_of_few_rows_takes_any_workspace():
+    """Up to 32 rows, as before the tiled kernel took some of them, a workspace
+    that it cannot use does not matter."""
+    a, w = _bf16((20, 12288), 67).to(DEV), _bf16((4096, 12288), 68, 0.05).to(DEV)
+    out = torch.empty(20, 4096, dtype=torch.bfloat16, device=DEV)
+    ws = torch.empty(1 << 24, dtype=torch.uint8, device=DEV)[8:]
+    M.project_attn(a, w, out, ws=ws)
+    torch.cuda.synchronize()
+    want = _f64(a) @ _f64(w).T
+    slack = 2.0 ** -20 * (np.abs(_f64(a)) @ np.abs(_f64(w)).T)
+    assert np.all(np.abs(_f64(out) - want) <= 2.0 ** -8 * np.abs(want) + slack + 1e-6)
+
+
 def _small_model():
     cfg = M.ModelConfig(hidden=256, layers=1, hq=4, hkv=2, head_dim=64, inter=512, vocab=1000,
                         theta=1e4)
