@@ -11,8 +11,9 @@ scheduler's batch through every layer of such a model with synthetic weights:
 
 Every step runs in this package's HIP kernels (libcplayer.so for the
 projections and the element-wise parts, libcpattn.so for append and
-attention); projections of shapes or tensors that those do not take run as
-library GEMMs (torch.mm / addmm, i.e. hipBLASLt).  Each layer has
+attention); the largest of the feed-forward's projections, and those of shapes
+or tensors that the kernels do not take, run as library GEMMs (torch.mm /
+addmm, i.e. hipBLASLt).  Each layer has
 its own paged KV pool; all layers share one block table, whose row s maps
 slot s's logical blocks to physical blocks (a random permutation, so pages
 are scattered).  Weights are N(0, 0.02) in bf16, norms 1.
@@ -263,21 +264,47 @@ def _tiled_takes(a, w, out, residual):
                                      or _apart(residual, out)))
 
 
+# Above 32 rows, where the library beats the tiled kernel (us, library / tiled,
+# weights from HBM).  Long rows (K >= N) gain from the split over K: 4096 x
+# 12288 121 / 92 at 1,000 rows, 186 / 161 at 2,048; 2048 x 6144 99 / 88 still at
+# 4,096; only large ones past 2,048 rows lose (4096 x 12288 205 / 219 at 2,560,
+# 286 / 277 at 4,096; 8192 x 28672 940 / 996 at 2,560).  Wide ones are bound by
+# the products, and large ones run at a higher rate in the library: 24576 x 4096
+# 49 / 42 at 100 rows, 88 / 83 at 512, 167 / 160 at 1,000, 164 / 160 at 1,024,
+# but 184 / 188 at 1,100, 279 / 290 at 2,048, 542 / 561 at 4,096; 12288 x 2048
+# 90 / 86 at 2,048, 92 / 93 at 2,100, 147 / 153 at 4,096 (the library's own bad
+# sizes in between, 24576 x 4096 558 / 465 at 3,072, follow no rule).  Past 512
+# rows the tiles can also leave much of a round of 256 CUs idle: 22016 x 4096
+# 115 / 136 at 600 rows (0.53 of two rounds of 192 x 256), 28672 x 4096 134 /
+# 152 (0.68); 12288 x 2048 39.5 / 40.9 and 24576 x 4096 145 / 145 at 768 (0.75).
+def _library_fastest(m, n, k):
+    large = m * n * k > 1024 * 24576 * 4096
+    if k >= n:
+        return m > 2048 and large
+    if m <= 512:
+        return False
+    if m > 2048 or large:
+        return True
+
+    def busy(rows, columns):   # share of the CUs' rounds
+        rounds = -(-(-(-m // rows) * (n // columns)) // 256)
+        return m * n / (rounds * 256 * rows * columns)
+    tiles = [t for t in ((256, 256), (192, 256), (256, 192)) if n % t[1] == 0]
+    return bool(tiles) and max(busy(*t) for t in tiles) < 0.78
+
+
 def project(a, w, out, residual=None, stream=None, ws=None):
     """a @ w^T into out (+ residual), on the package's kernels like
     project_attn where they take the shapes and tensors, else on the platform
-    BLAS.  The feed-forward and LM-head projections use it.
-
-    The tiled kernel against hipBLASLt (weights from HBM): gate/up (24576 x
-    4096) 44.9 -> 38.0 us at 24 rows, 48.9 -> 45.5 at 96, 72.2 -> 65.7 at 261,
-    164.4 -> 161.9 at 1,000, 279.6 -> 294.0 at 2,048; down (4096 x 12288) 24.8
-    -> 20.3, 55.9 -> 28.6, 67.4 -> 44.0, 115.4 -> 92.9, 180.9 -> 160.2."""
+    BLAS (_library_fastest, _tiled_takes).  The feed-forward and LM-head
+    projections use it.  Without ``ws`` the split's partials are allocated here:
+    fp32, at most 8 x rows x N (65 MB for 4096 x 12288 at 1,000 rows)."""
     import torch
     M, K = a.shape
     N = w.shape[0]
     if _skinny_fastest(M, N, K):
         gemm_skinny(a, w, out, residual, stream)
-    elif _tiled_takes(a, w, out, residual):
+    elif not _library_fastest(M, N, K) and _tiled_takes(a, w, out, residual):
         gemm(a, w, out, residual, stream, ws)
         if not skinny_faster(M, N, K) and not out.is_inference():
             torch.autograd.graph.increment_version(out)   # as torch's product does
