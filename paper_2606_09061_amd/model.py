@@ -21,6 +21,7 @@ are scattered).  Weights are N(0, 0.02) in bf16, norms 1.
 
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import math
 import os
@@ -156,18 +157,24 @@ def gemm_workspace_bytes(m, n, k):
     return int(load().cpl_gemm_workspace_bytes(m, n, k))
 
 
+def _on(stream, device):
+    """Makes a `stream` argument torch's current stream (None: it stays)."""
+    import torch
+    if stream is None or device.type != "cuda":
+        return contextlib.nullcontext()
+    if isinstance(stream, int):
+        stream = (torch.cuda.ExternalStream(stream, device=device) if stream
+                  else torch.cuda.default_stream(device))
+    return torch.cuda.stream(stream)
+
+
 def _scratch(nbytes, device, stream):
     """Device bytes that belong to the stream the kernels run on, so that the
     allocator hands them out again only behind those kernels; None when there
     are none to be had."""
     import torch
     try:
-        if stream is None:   # the current stream, torch's own choice
-            return torch.empty(nbytes, dtype=torch.uint8, device=device)
-        if isinstance(stream, int):
-            stream = (torch.cuda.ExternalStream(stream, device=device) if stream
-                      else torch.cuda.default_stream(device))
-        with torch.cuda.stream(stream):
+        with _on(stream, device):
             return torch.empty(nbytes, dtype=torch.uint8, device=device)
     except torch.cuda.OutOfMemoryError:
         return None
@@ -310,12 +317,14 @@ def project(a, w, out, residual=None, stream=None, ws=None):
             torch.autograd.graph.increment_version(out)   # as torch's product does
     elif skinny_faster(M, N, K):
         gemm_skinny(a, w, out, residual, stream)
-    elif residual is None:
-        torch.mm(a, w.t(), out=out)
-    elif residual is out:
-        out.addmm_(a, w.t())
     else:
-        torch.addmm(residual, a, w.t(), out=out)
+        with _on(stream, a.device):
+            if residual is None:
+                torch.mm(a, w.t(), out=out)
+            elif residual is out:
+                out.addmm_(a, w.t())
+            else:
+                torch.addmm(residual, a, w.t(), out=out)
 
 
 @dataclass

@@ -170,6 +170,25 @@ def _torch_operands(rows=45):
             _bf16((rows, 256), 66).to(DEV))
 
 
+@pytest.mark.parametrize("handle", [False, True])
+def test_project_left_to_the_library_runs_on_the_given_stream(handle):
+    """A strided operand is the library's; its product follows the work on the
+    stream that project() is given, not on the current one."""
+    from paper_2606_09061_amd import model as MM
+    a, w, x = _torch_operands()
+    ws = torch.zeros(256, 1088, dtype=torch.bfloat16, device=DEV)[:, :1024]
+    out = torch.zeros_like(x)
+    torch.mm(a, w.t(), out=x)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream(DEV)
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(20_000_000)     # milliseconds
+        ws.copy_(w)
+    MM.project(a, ws, out, None, side.cuda_stream if handle else side)
+    side.synchronize()
+    assert torch.equal(out, x)
+
+
 def test_project_in_forward_mode():
     """Inside a dual level the products above the skinny kernel's batch sizes
     are torch's: refused into a given tensor, with their tangent in place."""
