@@ -120,24 +120,42 @@ def skinny_faster(m, n, k):
     return m <= 32
 
 
-# Where, of those, the skinny kernel beats the tiled one too.  Per launch,
-# weights from HBM, skinny / tiled us: QKV (6144 x 4096) 11.4 / 13.0 at 1 row,
-# 11.9 / 13.8 at 16, 13.1 / 14.2 at 24, 14.8 / 14.6 at 32; gate/up (24576 x
-# 4096) 31.3 / 36.5, 33.4 / 37.3, 37.9 / 38.0, 42.3 / 39.5.  Long rows (K > N:
-# the down projection) need more workgroups than their column slices give,
-# which the tiled kernel's split over K has: 4096 x 12288 21.1 / 19.3 at 8
-# rows, 21.9 / 19.8 at 16, 31.3 / 21.0 at 32.  Wide projections stream their
-# activations again for every slice and lose from 17 rows (LM head, 151936 x
-# 4096: 196.7 / 192.1 at 16, 209.2 / 193.8 at 20).  Below 32 M weights a step
-# of the layer waits for the host, and the split's second launch and scratch
-# cost more than the kernel gains (down 2048 x 6144 10.8 / 9.2 at 8 rows, but
-# its feed-forward block 31 / 45 us; the projections around the step at hidden
-# 4,096, 32 rows, 34.3 / 37.7).  The tiled kernel takes N % 128 == 0 only.
+# Where, of those, the skinny kernel is the faster one too (skinny / tiled us a
+# launch, weights from HBM, at the row counts named):
+# * Up to 7 rows; where N is not a multiple of 128 there is only the skinny one.
+# * Up to 32 M weights.  QKV (6144 x 4096) 11.4 / 13.0 at 1 row, 13.1 / 14.2 at
+#   24, 14.8 / 14.6 at 32; 8192 x 4096 13.2 / 15.0 at 17, 14.8 / 15.6 at 28.
+#   Below, a step of the layer waits for the host, and the split's second
+#   launch and scratch cost more than the kernel gains (down 2048 x 6144 10.8 /
+#   9.2 at 8 rows, but its feed-forward block 31 / 45; the projections around
+#   the step at hidden 4,096, 32 rows, 34.3 / 37.7).
+# * Up to 16 rows otherwise: gate/up (24576 x 4096) 33.7 / 35.8 at 16; each
+#   slice of columns streams the activations again, so that it loses with more
+#   rows (gate/up 36.8 / 36.3 at 20, 42.3 / 37.7 at 32; LM head, 151936 x 4096,
+#   196 / 194 at 16, 209 / 196 at 20).  N below 8,192 lasts to 24 (7168 x 7168
+#   20.0 / 20.8 at 17, 21.9 / 21.8 at 24).
+# * Up to 20 rows where its slices of 32 columns fill the CUs' rounds and the
+#   tiles of 64 do not: gate/up 33.7 / 36.0 at 17, 35.1 / 36.1 at 19; 22016 x
+#   4096 32.8 / 35.7 at 17; but 16384 x 4096 (whole rounds of tiles) 24.4 / 22.9
+#   at 20, and with longer rows 8192 x 8192 29.7 / 25.7 at 17.
+# * Long rows (K > N) up to 12, if the slices fill the CUs: 8192 x 28672 69.5 /
+#   73.8 at 8, 73.3 / 73.8 at 16; 8192 x 12288 33.6 / 34.5 at 12, 34.7 / 33.4 at
+#   16.  Else they need more workgroups than the slices give, which the tiled
+#   kernel's split over K has: 4096 x 12288 21.2 / 19.2 at 8, 31.8 / 20.8 at 32;
+#   12288 x 14336 63.4 / 55.4 at 8.
 def _skinny_fastest(m, n, k):
     if m > 32 or n % 32 or k % 256 or m < 1:
         return False
-    return (m < 8 or n * k < 32 << 20 or n % 128 != 0
-            or (k <= n and (m <= 16 or (m <= 24 and n < 8192))))
+    if m < 8 or n * k <= 32 << 20 or n % 128 != 0:
+        return True
+    if k <= n and (m <= 16 or (m <= 24 and n < 8192)):
+        return True
+
+    def filled(workgroups):   # share of whole rounds of 256 CUs
+        return workgroups / (-(-workgroups // 256) * 256)
+    if filled(n // 32) < 8 / 9:
+        return False
+    return m <= 12 if k > n else m <= 20 and k <= 4096 and filled(n // 64) <= 0.75
 
 
 def gemm_skinny(a, w, out, residual=None, stream=None):

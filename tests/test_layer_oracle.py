@@ -125,13 +125,19 @@ def test_positions_of_rows():
 
 
 def test_skinny_dispatch_follows_measured_table():
-    from paper_2606_09061_amd.model import skinny_faster
-    qkv, o, gate_up, down = (6144, 4096), (4096, 4096), (24576, 4096), (4096, 12288)
-    for n, k in (qkv, o, gate_up, down):
-        assert skinny_faster(1, n, k) and skinny_faster(16, n, k)
-        assert not skinny_faster(33, n, k) and not skinny_faster(128, n, k)
-    assert skinny_faster(32, *qkv) and skinny_faster(32, *gate_up) and skinny_faster(32, *down)
-    assert not skinny_faster(1, 1000, 256) and not skinny_faster(1, 64, 320)   # unsupported shapes
+    """The largest batch of each projection that the skinny kernel takes."""
+    from paper_2606_09061_amd.model import _skinny_fastest, skinny_faster
+    last = {(6144, 4096): 32, (4096, 4096): 32, (8192, 4096): 32,    # up to 32 M weights
+            (24576, 4096): 20, (22016, 4096): 20, (16384, 4096): 16, (151936, 4096): 16,
+            (8192, 8192): 16, (10240, 8192): 16, (7168, 7168): 24,
+            (4096, 12288): 7, (12288, 14336): 7, (8192, 12288): 12, (8192, 28672): 12,
+            (12320, 4096): 32}                                       # N % 128: only the skinny one
+    for (n, k), rows in last.items():
+        taken = [m for m in range(1, 40) if _skinny_fastest(m, n, k)]
+        assert taken == list(range(1, rows + 1)), (n, k, taken[-1])
+        assert all(skinny_faster(m, n, k) for m in taken)
+    for f in (skinny_faster, _skinny_fastest):   # unsupported shapes
+        assert not f(1, 1000, 256) and not f(1, 64, 320) and not f(0, 64, 256)
 
 
 def test_library_dispatch_follows_measured_table():
