@@ -616,13 +616,12 @@ constexpr Cfg kCfgs[] = {
     stream_cfg<2, 4, 1, 1, 6>(0.213f, 3.5f), // 16: 32 x 64
 };
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
-constexpr int kDefaultCfg = 8;  // divides every N
-// for K an odd number of 32s
-constexpr Cfg kHalf64 = stream_cfg<2, 4, 2, 2, 3, true>(0.f, 0.f);
-constexpr Cfg kHalf128 = stream_cfg<2, 4, 4, 2, 4, true>(0.f, 0.f);
+// for K an odd number of 32s (times as of the same tiles above)
+constexpr Cfg kHalf64 = stream_cfg<2, 4, 2, 2, 3, true>(0.393f, 5.2f);
+constexpr Cfg kHalf128 = stream_cfg<2, 4, 4, 2, 4, true>(0.520f, 6.3f);
 // for any K, of which 7 rows and a row's chunk may pass 32 bits of byte offset
 constexpr int kMaxNearK = (int)((0xffffffffu - kRow) / 14);
-constexpr Cfg kFar = stream_cfg<2, 4, 2, 2, 3, true, true>(0.f, 0.f);
+constexpr Cfg kFar = stream_cfg<2, 4, 2, 2, 3, true, true>(0.393f, 5.2f);
 
 int env_int(const char* name, int dflt) {
   const char* s = getenv(name);
@@ -654,17 +653,11 @@ float estimate(const Cfg& f, int M, int N, int K, int S) {
 void choose(int M, int N, int K, size_t ws_floats, const Cfg** cfg, int* split) {
   const int stages = (K + kStageK - 1) / kStageK;
   const int forced_cfg = env_int("CPL_GEMM_CFG", -1), forced_split = env_int("CPL_GEMM_SPLIT", 0);
-  const bool half = K % kStageK != 0;
   const Cfg* best = nullptr;
   int best_split = 1;
   float best_us = 0.f;
   auto fits = [&](int s) { return s <= 1 || (size_t)s * (size_t)M * (size_t)N <= ws_floats; };
-  for (int c = 0; c < kNumCfgs; ++c) {
-    const Cfg& f = kCfgs[c];
-    if (N % f.bn != 0) continue;
-    if (forced_cfg >= 0 && forced_cfg < kNumCfgs && c != forced_cfg &&
-        N % kCfgs[forced_cfg].bn == 0)
-      continue;
+  auto consider = [&](const Cfg& f) {
     const int64_t tiles = (int64_t)((M + f.bm - 1) / f.bm) * (N / f.bn);
     for (int s = 1; s <= kMaxSplit; ++s) {
       if (forced_split > 0) {
@@ -677,10 +670,20 @@ void choose(int M, int N, int K, size_t ws_floats, const Cfg** cfg, int* split) 
       const bool better = !best || (forced_split > 0 && best == &f) || us < best_us;
       if (better) best = &f, best_split = s, best_us = us;
     }
+  };
+  if (K > kMaxNearK) {
+    consider(kFar);
+  } else if (K % kStageK != 0) {
+    consider(M <= 64 ? kHalf64 : kHalf128);
+  } else {
+    for (int c = 0; c < kNumCfgs; ++c) {
+      if (N % kCfgs[c].bn != 0) continue;
+      if (forced_cfg >= 0 && forced_cfg < kNumCfgs && c != forced_cfg &&
+          N % kCfgs[forced_cfg].bn == 0)
+        continue;
+      consider(kCfgs[c]);
+    }
   }
-  if (!best) best = &kCfgs[kDefaultCfg];
-  if (half) best = M <= 64 ? &kHalf64 : &kHalf128;
-  if (K > kMaxNearK) best = &kFar;
   *cfg = best;
   *split = best_split;
 }

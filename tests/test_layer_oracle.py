@@ -197,3 +197,14 @@ def test_gemm_validates_before_launching():
     assert lib.cpl_gemm_workspace_bytes(4096, 6144, 4096) == 0
     assert lib.cpl_gemm_workspace_bytes(64, 4096, 4096) > 0
     assert lib.cpl_gemm_workspace_bytes(8, 96, 32) == 0
+
+
+def test_gemm_split_of_half_stages_suits_their_own_tile():
+    """K an odd number of 32s runs on one tile per batch size: its split is the
+    one that suits that tile (2,048 rows fill the GPU twice over; 256 rows give
+    it 64 tiles)."""
+    from paper_2606_09061_amd import model as M
+    size = M.load().cpl_gemm_workspace_bytes
+    assert size(2048, 4096, 12320) == 0 and size(512, 6144, 2080) == 0
+    assert size(256, 4096, 4128) >= 2 * 256 * 4096 * 4
+    assert size(64, 6144, 2080) >= 2 * 64 * 6144 * 4
