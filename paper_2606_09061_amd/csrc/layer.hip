@@ -13,7 +13,6 @@
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kNormHeld = 2;
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
@@ -46,32 +45,33 @@ __device__ __forceinline__ float sumsq8(const uint4& a) {
 
 // One block per row.  x and out may alias: every element is read and then
 // written by the same thread, after the block-wide reduction barrier.
-// The first kNormHeld pieces of a thread (rows of up to 4,096 elements: all
-// of them) and their weights are loaded together and stay in registers.  A
-// decode batch's launch is bound by its dependent round trips to memory; the
-// row and the weights loaded again behind the barrier were a second one.  us a
-// launch at width 4,096, loaded twice / once: 1 row 2.93 / 2.59, 24 rows 3.19 /
-// 2.87, 1,000 rows 4.6 / 4.3, 1,500 rows 5.41 / 5.31, 2,048 rows 6.40 / 6.51.
+// The first HELD pieces of a thread and their weights are loaded together and
+// stay in registers.  A decode batch's launch is bound by its dependent round
+// trips to memory; the row and the weights loaded again behind the barrier were
+// a second one.  us a launch at width 4,096, loaded twice / once: 1 row 2.42 /
+// 2.11, 24 rows 2.66 / 2.33, 1,000 rows 5.05 / 4.68, 2,048 rows 7.29 / 6.81,
+// 8,192 rows 25.0 / 21.6.
+template <int HELD>
 __global__ __launch_bounds__(kThreads, 8) void rmsnorm_kernel(const uint4* x, const uint4* w,
                                                            uint4* out, int width8,
                                                            float inv_width, float eps) {
   const size_t row = blockIdx.x;
   const uint4* xr = x + row * width8;
   uint4* orow = out + row * width8;
-  uint4 xv[kNormHeld], wv[kNormHeld];
+  uint4 xv[HELD + 1], wv[HELD + 1];
 #pragma unroll
-  for (int i = 0; i < kNormHeld; ++i) {
+  for (int i = 0; i < HELD; ++i) {
     const int v = min((int)threadIdx.x + i * kThreads, width8 - 1);  // past the row: unused
     xv[i] = xr[v];
     wv[i] = w[v];
   }
   float ss = 0.f;
 #pragma unroll
-  for (int i = 0; i < kNormHeld; ++i)
+  for (int i = 0; i < HELD; ++i)
     ss += (int)threadIdx.x + i * kThreads < width8 ? sumsq8(xv[i]) : 0.f;
-  for (int v = threadIdx.x + kNormHeld * kThreads; v < width8; v += kThreads) ss += sumsq8(xr[v]);
+  for (int v = threadIdx.x + HELD * kThreads; v < width8; v += kThreads) ss += sumsq8(xr[v]);
 #pragma unroll
-  for (int i = 0; i < kNormHeld; ++i)  // w's loads are not moved past the barrier below
+  for (int i = 0; i < HELD; ++i)  // w's loads are not moved past the barrier below
     asm volatile("" : "+v"(wv[i].x), "+v"(wv[i].y), "+v"(wv[i].z), "+v"(wv[i].w));
   ss = wave_sum(ss);
   __shared__ float part[kThreads / 64];
@@ -90,11 +90,11 @@ __global__ __launch_bounds__(kThreads, 8) void rmsnorm_kernel(const uint4* x, co
     orow[v] = make_uint4(o[0], o[1], o[2], o[3]);
   };
 #pragma unroll
-  for (int i = 0; i < kNormHeld; ++i) {
+  for (int i = 0; i < HELD; ++i) {
     const int v = threadIdx.x + i * kThreads;
     if (v < width8) store(v, xv[i], wv[i]);
   }
-  for (int v = threadIdx.x + kNormHeld * kThreads; v < width8; v += kThreads)
+  for (int v = threadIdx.x + HELD * kThreads; v < width8; v += kThreads)
     store(v, xr[v], w[v]);
 }
 
@@ -389,7 +389,12 @@ int cpl_rmsnorm(const void* x, const void* w, void* out, int32_t n_rows, int32_t
   if (!x || !w || !out || !aligned16(x) || !aligned16(w) || !aligned16(out))
     return CP_ERR_INVALID_ARG;
   (void)hipGetLastError();
-  hipLaunchKernelGGL(rmsnorm_kernel, dim3(n_rows), dim3(kThreads), 0, (hipStream_t)stream,
+  // rows of up to 2,048 elements have one piece a thread; up to 1,024, where half
+  // the waves have none, loading it once lost (2,048 rows 3.23 -> 3.62 us; with a
+  // second, idle piece 2,048 x 1,280 rows 3.52 -> 3.64)
+  auto kern = width <= 1024 ? rmsnorm_kernel<0> : width <= 2048 ? rmsnorm_kernel<1>
+                                                                : rmsnorm_kernel<2>;
+  hipLaunchKernelGGL(kern, dim3(n_rows), dim3(kThreads), 0, (hipStream_t)stream,
                      (const uint4*)x, (const uint4*)w, (uint4*)out, width / 8, 1.0f / width, eps);
   return launched();
 }

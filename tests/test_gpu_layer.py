@@ -38,7 +38,8 @@ def _close(got, want, rel=2.0 ** -8, abs_=1e-5):
     assert np.all(err <= bound), f"max excess {np.max(err - bound):.3e}, max err {err.max():.3e}"
 
 
-@pytest.mark.parametrize("n,width", [(1, 8), (37, 4096), (5, 12288), (3, 520)])
+@pytest.mark.parametrize("n,width", [(1, 8), (37, 4096), (5, 12288), (3, 520), (3, 1024), (5, 1032),
+                                     (2, 2048), (4, 2056), (3, 4104)])
 def test_rmsnorm_matches_reference(n, width):
     print(f"rmsnorm n={n} width={width}", flush=True)
     x = _bf16((n, width), 1, 3.0)
@@ -50,8 +51,17 @@ def test_rmsnorm_matches_reference(n, width):
 
 
 def test_rmsnorm_in_place():
-    x = _bf16((9, 1024), 3).to(DEV)
-    w = _bf16((1024,), 4).to(DEV)
+    _rmsnorm_in_place(1024)
+
+
+@pytest.mark.parametrize("width", [2048, 4096])
+def test_rmsnorm_in_place_of_held_rows(width):
+    _rmsnorm_in_place(width)
+
+
+def _rmsnorm_in_place(width):
+    x = _bf16((9, width), 3).to(DEV)
+    w = _bf16((width,), 4).to(DEV)
     want = ref.rmsnorm(_f64(x), _f64(w), 1e-6)
     M.rmsnorm(x, w, x, 1e-6)
     torch.cuda.synchronize()
