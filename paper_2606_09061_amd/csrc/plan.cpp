@@ -573,9 +573,10 @@ void build_plan(const cp_attn_desc& d, const cp_row_meta* rows, int32_t n_rows,
     }
   };
   sc.dec_groups.clear();
-  int64_t dec_blocks = 0;
+  int64_t dec_blocks = 0, dec_rows = 0;
   int32_t dec_longest = 0;
   each_decode_token([&](const cp_row_meta&, int32_t, int32_t kv_end) {
+    ++dec_rows;
     dec_blocks += ceil_div(kv_end, B) * Hkv;
     dec_longest = std::max(dec_longest, kv_end);
   });
@@ -586,12 +587,27 @@ void build_plan(const cp_attn_desc& d, const cp_row_meta* rows, int32_t n_rows,
     // partial rows for the merge and a workgroup's start-up, rising to 3 (6)
     // per CU at 4 GB and above, where finer items balance the tail better.
     // Step us on the matrix cores at 1 / 1.5 / 2 / 3 / 4 per CU: 8 rows of
-    // 14.9 k keys 25.7 / 24.0 / 24.8 / 26.4 / 30.8; 512-token budget mix (0.88
-    // GB) 153.6 / 153.1 / 152.6 / 156.0 / 159.2; 256 decode rows (7 GB) 1071 /
-    // 1069 / 1088 / 1066 / 1071.
+    // 14.9 k keys 25.7 / 24.0 / 24.8 / 26.4 / 30.8; beside prefill chunks,
+    // 512-token budget mix (0.88 GB) 153.6 / 153.1 / 152.6 / 156.0 / 159.2;
+    // 256 decode rows and a chunk (7 GB) 1071 / 1069 / 1088 / 1066 / 1071.
     const double dec_bytes = (double)dec_blocks * B * d.head_dim * 4.0;
-    const double rise = G >= kDecodeMfmaMinGroup ? 0.5 : 1.0;
+    const bool mfma = G >= kDecodeMfmaMinGroup;
+    const double rise = mfma ? 0.5 : 1.0;
     double per_cu = t.decode_units_per_cu * (1.0 + rise * std::min(1.0, dec_bytes / 4.0e9));
+    // A launch of matrix-core units alone: 3 per CU rising to 4.5 at 0.5 GB,
+    // from 0.09 GB on (D = 64: 0.18), with fewer rows than about the CUs (per kv head)
+    // from 0.2.  At 2 to 3 per CU the last units ran alone for long, and at G =
+    // 4 such steps were slower than on the vector units.  us on those, at 2 to
+    // 3 per CU / by this rule: 32/8 heads, 32 rows of 31 k keys (0.13 GB) 37.5,
+    // 38.2 / 37.0; 103 of 77 k 69.8, 71.2 / 69.6; 200 of 280 k 208, 214 / 205;
+    // 256 of 950 k 635, 662 / 633; with D = 64, 128 of 214 k (0.44 GB) 84.9,
+    // 91.1 / 85.2; 64/8 heads, 200 of 280 k 280, 230 / 222.  Few rows are cut
+    // into many units anyhow: 8 rows of 26 k (0.11 GB) 32.3, 29.6 / 31.1 at 3;
+    // 16/4 heads, 24 of 61 k (0.12 GB) 36.7, 32.4 / 35.9.
+    const bool many = dec_rows * Hkv * 4 >= 3 * (int64_t)t.num_cus;
+    if (mfma && !fused && settings.decode_units_per_cu <= 0.0 &&
+        dec_bytes >= (many ? 0.09e9 * 128 / d.head_dim : 0.2e9))
+      per_cu = 3.0 + 1.5 * std::min(1.0, dec_bytes / 0.5e9);
     // Inside a prefill-dominated launch, longer decode ranges: each unit
     // streams beside the tiles for much of the launch.  Only rows longer than
     // the cut are split, so this sets the longest unit (measured best at

@@ -296,6 +296,28 @@ def test_fused_steps_use_128_row_tiles_and_fewer_decode_units(monkeypatch):
     assert w == 64 and units0 > units
 
 
+def test_decode_units_of_a_launch_of_their_own(monkeypatch):
+    """Decode rows without prefill chunks on the matrix cores (4 q heads per kv
+    head): about 3 units per CU and more, but 2 for small loads, for few rows,
+    and beside a chunk; a setting of CP_DECODE_UNITS_PER_CU holds."""
+    monkeypatch.setenv("CP_NUM_CUS", "256")
+    d = _desc(num_blocks=200000, max_blocks_per_req=4096, num_reqs_in_table=300)
+
+    def per_cu(ctx, chunk=0):
+        rows = [[i, c - 1, 1, c] for i, c in enumerate(ctx)]
+        if chunk:
+            rows.append([len(rows), 0, chunk, chunk])
+        items = cp.plan_items(d, np.array(rows, np.int32))
+        return int((items[:, 0] == 1).sum()) / 256
+
+    long, many, few = [12000] * 20, [1300] * 30, [6000] * 4      # 0.98, 0.16 and 0.10 GB
+    assert per_cu(long) >= 4.5 and per_cu(many) >= 3.4
+    assert per_cu(long, chunk=16) <= 2.6
+    assert per_cu(few) <= 2.2
+    monkeypatch.setenv("CP_DECODE_UNITS_PER_CU", "2")
+    assert per_cu(long) <= 2.6 and per_cu(many) <= 2.9
+
+
 FEW_TOKEN_ROWS = [(0, 2), (5, 3), (100, 2), (4000, 7), (31, 15), (16, 16), (999, 1), (0, 1),
                   (2047, 40), (3, 0)]
 
