@@ -311,7 +311,8 @@ def test_decode_units_of_a_launch_of_their_own(monkeypatch):
         return int((items[:, 0] == 1).sum()) / 256
 
     long, many, few = [12000] * 20, [1300] * 30, [6000] * 4      # 0.98, 0.16 and 0.10 GB
-    assert per_cu(long) >= 4.5 and per_cu(many) >= 3.4
+    # (units are whole splits of a row: 7 of 108 blocks, 4 of 24)
+    assert per_cu(long) >= 4.0 and per_cu(many) >= 3.4
     assert per_cu(long, chunk=16) <= 2.6
     assert per_cu(few) <= 2.2
     monkeypatch.setenv("CP_DECODE_UNITS_PER_CU", "2")
