@@ -299,9 +299,10 @@ def _tiled_takes(a, w, out, residual):
 # but 184 / 188 at 1,100, 279 / 290 at 2,048, 542 / 561 at 4,096; 12288 x 2048
 # 90 / 86 at 2,048, 92 / 93 at 2,100, 147 / 153 at 4,096 (the library's own bad
 # sizes in between, 24576 x 4096 558 / 465 at 3,072, follow no rule).  Past 512
-# rows the tiles can also leave much of a round of 256 CUs idle: 22016 x 4096
-# 115 / 136 at 600 rows (0.53 of two rounds of 192 x 256), 28672 x 4096 134 /
-# 152 (0.68); 12288 x 2048 39.5 / 40.9 and 24576 x 4096 145 / 145 at 768 (0.75).
+# rows, tiles that leave much of a round of 256 CUs idle lose where padded rows
+# are a good part of it: 22016 x 4096 115 / 136 at 600 rows (0.53 of two rounds
+# of 192 x 256, 600 rows of 768), 28672 x 4096 134 / 152 (0.68); but 24576 x
+# 4096 147 / 142 at 700 (0.68, 700 rows of 768), 145 / 145 at 768 (0.75).
 def _library_fastest(m, n, k):
     large = m * n * k > 1024 * 24576 * 4096
     if k >= n:
@@ -314,6 +315,8 @@ def _library_fastest(m, n, k):
     def busy(rows, columns):   # share of the CUs' rounds
         rounds = -(-(-(-m // rows) * (n // columns)) // 256)
         return m * n / (rounds * 256 * rows * columns)
+    if m >= 0.85 * -(-m // 192) * 192 or m >= 0.85 * -(-m // 256) * 256:
+        return False
     tiles = [t for t in ((256, 256), (192, 256), (256, 192)) if n % t[1] == 0]
     return bool(tiles) and max(busy(*t) for t in tiles) < 0.78
 
