@@ -46,11 +46,13 @@ cpattn::Tuning random_tuning(std::mt19937& g) {
   t.fuse_decode = pick(5);
   const double spread[] = {1.0, 0.0, 0.3};
   t.fuse_spread = spread[pick(3)];
-  const double kps[] = {64.0, 1.0, 1000.0};
-  t.fuse_keys_per_step = kps[pick(3)];
+  const double kps[] = {0.0, 64.0, 1.0, 1000.0};  // 0: by group, as below
+  t.fuse_keys_per_step = kps[pick(4)];
   t.fuse_narrow = pick(2) != 0;
-  const double upc[] = {0.75, 0.01, 4.0};
-  t.fuse_units_per_cu = upc[pick(3)];
+  const double upc[] = {0.0, 0.75, 0.01, 4.0};
+  t.fuse_units_per_cu = upc[pick(4)];
+  const double dupc[] = {0.0, 2.0, 0.01, 40.0};
+  t.decode_units_per_cu = dupc[pick(4)];
   const double fpb[] = {180.0, 0.0, 1e9};
   t.fuse_flops_per_byte = fpb[pick(3)];
   t.xcd_piece_div = pick(10);

@@ -152,9 +152,21 @@ def test_project_of_every_form(rows, form):
     elif form == "residual_overlaps_out":
         if rows <= 32:
             pytest.skip("the skinny kernel's batch sizes: residual apart from out, or out itself")
-        buf = torch.empty((rows + 1) * N, dtype=torch.bfloat16, device=DEV)
-        out, rd = buf[:rows * N].view(rows, N), buf[N:].view(rows, N)
+        def overlapping():   # the residual lies one row further on
+            buf = torch.empty((rows + 1) * N, dtype=torch.bfloat16, device=DEV)
+            buf[N:] = r.to(DEV).view(-1)
+            return buf[:rows * N].view(rows, N), buf[N:].view(rows, N)
+        out, rd = overlapping()
         assert not MM._tiled_takes(ad, wd, out, rd)
+        want, copy = overlapping()   # torch's own answer, or its refusal
+        try:
+            torch.addmm(copy, ad, wd.t(), out=want)
+        except RuntimeError:
+            with pytest.raises(RuntimeError):
+                MM.project(ad, wd, out, rd)
+        else:
+            MM.project(ad, wd, out, rd)
+            assert torch.equal(out, want)
         return
     elif form == "autograd":
         wd = torch.nn.Parameter(wd)
@@ -487,6 +499,54 @@ def test_gemm_every_tile_matches_reference(monkeypatch, cfg, M, N, K, split):
     slack = 2.0 ** -20 * (np.abs(_f64(a)) @ np.abs(_f64(w)).T)
     err = np.abs(_f64(out) - want)
     assert np.all(err <= 2.0 ** -8 * np.abs(want) + slack + 1e-6), f"max err {err.max():.3e}"
+
+
+def _gemm_error_on_gpu(M, N, K, residual):
+    """cpl_gemm's largest excess over test_gemm_matches_reference's bound, and
+    whether every result is finite; the fp64 products by columns on the GPU."""
+    from paper_2606_09061_amd import model as MM
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+
+    def randn(*shape, scale=1.0):
+        return (torch.randn(*shape, generator=g, device=DEV) * scale).to(torch.bfloat16)
+    a, w, r = randn(M, K), randn(N, K, scale=0.05), randn(M, N)
+    out = r.clone() if residual else torch.full_like(r, float("nan"))
+    MM.gemm(a, w, out, out if residual else None)
+    excess = -math.inf
+    ad = a.double()
+    for n in range(0, N, 8192):
+        wd = w[n:n + 8192].double().t().contiguous()
+        want = ad @ wd + (r[:, n:n + 8192].double() if residual else 0.0)
+        bound = 2.0 ** -8 * want.abs() + 2.0 ** -20 * (ad.abs() @ wd.abs()) + 1e-6
+        excess = max(excess, float(((out[:, n:n + 8192].double() - want).abs() - bound).max()))
+    return excess, bool(torch.isfinite(out.float()).all())
+
+
+@pytest.mark.parametrize("M,N,K,residual", [
+    (24, 24576, 4096, False), (96, 24576, 4096, False), (261, 24576, 4096, False),
+    (300, 28672, 2048, False),
+    (45, 4096, 12288, True), (261, 4096, 12288, True),
+    (24, 151936, 512, False), (65, 151936, 512, True),   # more than two tiles per CU
+])
+def test_gemm_of_large_weights_matches_reference(M, N, K, residual):
+    """The forms that weights of 32 M elements and more take: copies that bypass
+    the caches in both kernels, and XCDs that start at the same stage where
+    there are more than two tiles per CU."""
+    print(f"gemm of large weights M={M} N={N} K={K}", flush=True)
+    excess, finite = _gemm_error_on_gpu(M, N, K, residual)
+    assert finite and excess <= 0.0
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 128, 416), (45, 256, 416), (64, 6144, 2080), (45, 384, 1056),
+                                   (130, 256, 1056), (2000, 1024, 2080)])
+@pytest.mark.parametrize("split", ["auto", "1", "3"])
+def test_gemm_of_half_stages_matches_reference(monkeypatch, M, N, K, split):
+    """K an odd number of 32s, many stages long, on both of its tiles."""
+    print(f"gemm of half stages M={M} N={N} K={K} split={split}", flush=True)
+    if split != "auto":
+        monkeypatch.setenv("CPL_GEMM_SPLIT", split)
+    excess, finite = _gemm_error_on_gpu(M, N, K, True)
+    assert finite and excess <= 0.0
 
 
 def _zeros_or_skip(*shape):
