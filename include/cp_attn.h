@@ -242,7 +242,8 @@ int64_t cp_plan_records(const cp_attn_desc *desc, const cp_row_meta *rows, int32
  * For callers that cannot allocate device memory per call: code that must
  * not call hipMalloc (under HIP graph capture, in tight serving loops, in
  * harnesses that forbid it).  cp_attn_mixed_noalloc runs the same plan and
- * kernels as cp_attn_mixed (identical output), but takes no workspace: its
+ * kernels as cp_attn_mixed (identical output; a plan of other decode unit
+ * sizes where only that one fits), but takes no workspace: its
  * plan lists and split partials live in a static device array of
  * CP_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on
  * until the process ends, and its plan is staged through two pinned host
@@ -256,7 +257,8 @@ int64_t cp_plan_records(const cp_attn_desc *desc, const cp_row_meta *rows, int32
  * cp_attn_mixed_noalloc: cp_attn_mixed's arguments without ws / ws_bytes,
  * same validation and codes, plus CP_ERR_WORKSPACE (nothing enqueued) when
  * the batch's workspace would exceed CP_NOALLOC_SCRATCH_BYTES or its plan
- * lists CP_NOALLOC_PLAN_BYTES (cp_workspace_bytes gives the former; the five
+ * lists CP_NOALLOC_PLAN_BYTES in both plans (cp_workspace_bytes gives the
+ * former for cp_attn_mixed's; the five
  * synthetic mixes of this library's benchmark need at most 42 MB), and
  * CP_ERR_INVALID_ARG when cp_noalloc_init has not run on the current device.
  * It calls no device or pinned allocator: it waits for the staging buffer's

@@ -857,9 +857,18 @@ int cp_attn_mixed_noalloc(const cp_attn_desc* desc, const void* q, const void* k
     // plan first: the size limits are host-side facts, checked before the
     // device is touched
     Plan& p = thread_plan();
-    build_plan(*desc, rows, n_rows, tuning_from_env(num_cus_setting()), p);
-    if (p.ws_bytes > CP_NOALLOC_SCRATCH_BYTES || p.plan_bytes > CP_NOALLOC_PLAN_BYTES)
-      return CP_ERR_WORKSPACE;
+    // Two plans are tried: with the matrix cores' longer decode units in its
+    // estimate a step may split its prefill tiles further than it did with the
+    // vector units', and what fitted then still runs.
+    Tuning t = tuning_from_env(num_cus_setting());
+    auto fits = [&] {
+      build_plan(*desc, rows, n_rows, t, p);
+      return p.ws_bytes <= CP_NOALLOC_SCRATCH_BYTES && p.plan_bytes <= CP_NOALLOC_PLAN_BYTES;
+    };
+    if (!fits()) {
+      t.vector_sizing = true;
+      if (!fits()) return CP_ERR_WORKSPACE;
+    }
     fill_plan(p, pl);
     uint8_t* ws = nullptr;
     Stage* st = nullptr;

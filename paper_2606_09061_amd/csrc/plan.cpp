@@ -491,7 +491,7 @@ static int64_t choose_split_steps(const cp_attn_desc& d, const Tuning& t,
 // and the vector units' kernel with its settings 157 | 625 | 153 | 297 | 291.
 // (Whole rows outlast the tiles at 0.25 to 0.375 units per CU.)
 static Tuning resolve_tuning(Tuning t, int G) {
-  const bool mfma = G >= kDecodeMfmaMinGroup;
+  const bool mfma = G >= kDecodeMfmaMinGroup && !t.vector_sizing;
   if (t.decode_units_per_cu <= 0.0) t.decode_units_per_cu = mfma ? 2.0 : 3.0;
   if (t.fuse_units_per_cu <= 0.0) t.fuse_units_per_cu = mfma ? 0.5 : 0.75;
   if (t.fuse_keys_per_step <= 0.0) t.fuse_keys_per_step = mfma ? 60.0 : 64.0;
@@ -591,7 +591,7 @@ void build_plan(const cp_attn_desc& d, const cp_row_meta* rows, int32_t n_rows,
     // 512-token budget mix (0.88 GB) 153.6 / 153.1 / 152.6 / 156.0 / 159.2;
     // 256 decode rows and a chunk (7 GB) 1071 / 1069 / 1088 / 1066 / 1071.
     const double dec_bytes = (double)dec_blocks * B * d.head_dim * 4.0;
-    const bool mfma = G >= kDecodeMfmaMinGroup;
+    const bool mfma = G >= kDecodeMfmaMinGroup && !t.vector_sizing;
     const double rise = mfma ? 0.5 : 1.0;
     double per_cu = t.decode_units_per_cu * (1.0 + rise * std::min(1.0, dec_bytes / 4.0e9));
     // A launch of matrix-core units alone: 3 per CU rising to 4.5 at 0.5 GB,

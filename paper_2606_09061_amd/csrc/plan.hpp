@@ -114,6 +114,8 @@ struct Tuning {
   double fuse_keys_per_step = 0.0;  // mode 4: decode keys worth one 64-key step of a tile (0: by
                                     // group)
   double decode_units_per_cu = 0.0;  // decode ranges per CU of small decode loads (0: by group)
+  bool vector_sizing = false;   // decode units sized as those on the vector units, whatever the
+                                // group (they run where the group says)
   bool fuse_narrow = true;      // a step with decode blocks in its prefill launch: 128-row tiles
   double fuse_units_per_cu = 0.0;    // decode ranges per CU that set the split length when
                                      // prefill dominates a fused step

@@ -48,6 +48,7 @@ cpattn::Tuning random_tuning(std::mt19937& g) {
   t.fuse_spread = spread[pick(3)];
   const double kps[] = {0.0, 64.0, 1.0, 1000.0};  // 0: by group, as below
   t.fuse_keys_per_step = kps[pick(4)];
+  t.vector_sizing = pick(4) == 0;
   t.fuse_narrow = pick(2) != 0;
   const double upc[] = {0.0, 0.75, 0.01, 4.0};
   t.fuse_units_per_cu = upc[pick(4)];

@@ -50,6 +50,28 @@ def test_noalloc_refuses_batches_beyond_its_scratch(monkeypatch):
                                      0, None, None) == binding.CP_OK
 
 
+def _two_plans_batch():
+    """A chunk after 32,000 keys beside four decode rows: cp_attn_mixed's plan
+    splits the chunk further than the scratch holds; sized as for the vector
+    units it fits."""
+    rows = [(32000, 300)] + [(15999, 1)] * 4
+    return make_batch("two plans", 32, 8, 128, 16, rows, np.random.default_rng(4))
+
+
+def test_noalloc_takes_the_plan_that_fits():
+    """Host only: without a device the accepted batch fails at its first device
+    call, and not for its size."""
+    if torch.cuda.is_available():
+        pytest.skip("stand-in addresses: for a host without a GPU")
+    b = _two_plans_batch()
+    d = cp.desc_for(b)
+    assert cp.workspace_bytes(d, b.rows) > binding.NOALLOC_SCRATCH_BYTES
+    r, fake = np.ascontiguousarray(b.rows), 1 << 20
+    rc = binding.load().cp_attn_mixed_noalloc(ctypes.byref(d), fake, fake, fake, fake,
+                                              r.ctypes.data, r.shape[0], fake, None)
+    assert rc == binding.CP_ERR_HIP
+
+
 def _run_both(batch, seed):
     """Appends with cp_kv_append, then cp_attn_mixed (caller workspace) and
     cp_attn_mixed_noalloc (static scratch) on the same inputs."""
@@ -99,3 +121,31 @@ def test_noalloc_matches_attn_mixed_on_two_calls():
         e = np.abs(g - ref)
         print(f"[gpu] noalloc {what}: max_abs={e.max():.3e} mean_abs={e.mean():.3e}", flush=True)
         assert np.isfinite(g).all() and e.max() <= MAX_ABS and e.mean() <= MEAN_ABS
+
+
+@pytest.mark.gpu
+def test_noalloc_with_the_plan_that_fits():
+    """The other plan's output.  Each is within 2.3e-3 (2-norm) of the exact one
+    (bf16 weights and output), so that they differ by at most about 5e-3."""
+    assert binding.load().cp_noalloc_init() == binding.CP_OK
+    batch = _two_plans_batch()
+    print(f"[gpu] noalloc two plans T={batch.num_tokens}", flush=True)
+    t = {k: v.to("cuda") for k, v in make_tensors(batch, seed=8803).items()}
+    d = cp.desc_for(batch)
+    need = cp.workspace_bytes(d, batch.rows)
+    assert need > binding.NOALLOC_SCRATCH_BYTES
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    out_ws = torch.empty(batch.num_tokens, 32, 128, dtype=torch.bfloat16, device="cuda")
+    out_na = torch.full_like(out_ws, float("nan"))
+    cp.kv_append(d, t["k_new"], t["v_new"], t["k_cache"], t["v_cache"], t["block_tables"],
+                 batch.rows, ws)
+    cp.attn_mixed(d, t["q"], t["k_cache"], t["v_cache"], t["block_tables"], batch.rows, out_ws, ws)
+    r = np.ascontiguousarray(batch.rows)
+    rc = binding.load().cp_attn_mixed_noalloc(
+        ctypes.byref(d), t["q"].data_ptr(), t["k_cache"].data_ptr(), t["v_cache"].data_ptr(),
+        t["block_tables"].data_ptr(), r.ctypes.data, r.shape[0], out_na.data_ptr(),
+        torch.cuda.current_stream().cuda_stream)
+    assert rc == binding.CP_OK, binding.strerror(rc)
+    torch.cuda.synchronize()
+    diff = (out_na.double() - out_ws.double()).norm() / out_ws.double().norm()
+    assert float(diff) <= 5e-3
