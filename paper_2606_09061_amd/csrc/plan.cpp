@@ -615,7 +615,19 @@ void build_plan(const cp_attn_desc& d, const cp_row_meta* rows, int32_t n_rows,
     // replay, with a cliff below 0.5 where whole long rows outlast the tiles;
     // decode-dominated steps keep the rule above).
     const double pf_flops = 4.0 * d.head_dim * d.num_q_heads * pf_keys;
-    if (fused && pf_flops > t.fuse_flops_per_byte * dec_bytes) per_cu = t.fuse_units_per_cu;
+    if (fused && pf_flops > t.fuse_flops_per_byte * dec_bytes) {
+      per_cu = t.fuse_units_per_cu;
+      // Four q heads per kv head: where 0.5 per CU cuts rows all the same,
+      // shorter units (0.6), or the longest outlast the tiles: the 2k-token
+      // prefill-heavy mix (rows to 32 k keys, 128 tile steps a slot) 618 us on
+      // the vector units, 633 at 0.5, 605 here.  Where it leaves all rows
+      // whole, whole ones stay better (1,700 tokens after 4k keys beside 64
+      // rows to 8k 198 / 209), as does 0.5 with eight heads (4,056 tokens
+      // beside 40 rows to 8k 133 / 138).
+      if (mfma && G == kDecodeMfmaMinGroup && settings.fuse_units_per_cu <= 0.0 &&
+          (double)dec_longest * t.num_cus * per_cu > (double)dec_blocks * B)
+        per_cu = 0.6;
+    }
     const int64_t target = t.decode_target_items > 0
                                ? t.decode_target_items
                                : std::max<int64_t>(1, (int64_t)(t.num_cus * per_cu));

@@ -319,6 +319,27 @@ def test_decode_units_of_a_launch_of_their_own(monkeypatch):
     assert per_cu(long) <= 2.6 and per_cu(many) <= 2.9
 
 
+def test_fused_decode_units_that_are_cut(monkeypatch):
+    """Beside a chunk that dominates the step: whole rows where half a unit per
+    CU leaves them whole; where it cuts them, shorter ones with four q heads per
+    kv head, the same with eight."""
+    monkeypatch.setenv("CP_NUM_CUS", "256")
+
+    def longest(hq, ctx):
+        d = _desc(num_q_heads=hq, num_blocks=200000, max_blocks_per_req=4096,
+                  num_reqs_in_table=300)
+        rows = [[i, c - 1, 1, c] for i, c in enumerate(ctx)]
+        rows.append([len(rows), 31000, 1000, 32000])
+        items = cp.plan_items(d, np.array(rows, np.int32))
+        dec = items[items[:, 0] == 1]
+        return int((dec[:, 7] - dec[:, 6]).max())
+
+    even, mixed = [3000] * 64, [2000] * 63 + [28800]
+    assert longest(32, even) == 3000 and longest(64, even) == 3000
+    # 154,800 keys by 8 heads in 128 or 153 units: the long row in 3 or 4
+    assert longest(64, mixed) == 9600 and longest(32, mixed) == 7200
+
+
 FEW_TOKEN_ROWS = [(0, 2), (5, 3), (100, 2), (4000, 7), (31, 15), (16, 16), (999, 1), (0, 1),
                   (2047, 40), (3, 0)]
 

@@ -51,11 +51,11 @@ def test_noalloc_refuses_batches_beyond_its_scratch(monkeypatch):
 
 
 def _two_plans_batch():
-    """A chunk after 32,000 keys beside four decode rows: cp_attn_mixed's plan
+    """A chunk after 8,000 keys beside eight decode rows: cp_attn_mixed's plan
     splits the chunk further than the scratch holds; sized as for the vector
     units it fits."""
-    rows = [(32000, 300)] + [(15999, 1)] * 4
-    return make_batch("two plans", 32, 8, 128, 16, rows, np.random.default_rng(4))
+    rows = [(8000, 1000)] + [(15999, 1)] * 8
+    return make_batch("two plans", 64, 8, 128, 32, rows, np.random.default_rng(4))
 
 
 def test_noalloc_takes_the_plan_that_fits():
@@ -135,7 +135,7 @@ def test_noalloc_with_the_plan_that_fits():
     need = cp.workspace_bytes(d, batch.rows)
     assert need > binding.NOALLOC_SCRATCH_BYTES
     ws = torch.empty(need, dtype=torch.uint8, device="cuda")
-    out_ws = torch.empty(batch.num_tokens, 32, 128, dtype=torch.bfloat16, device="cuda")
+    out_ws = torch.empty(batch.num_tokens, 64, 128, dtype=torch.bfloat16, device="cuda")
     out_na = torch.full_like(out_ws, float("nan"))
     cp.kv_append(d, t["k_new"], t["v_new"], t["k_cache"], t["v_cache"], t["block_tables"],
                  batch.rows, ws)
