@@ -53,7 +53,7 @@ constexpr int kStageK = 64;              // k per stage
 constexpr int kRow = kStageK * 2;        // bytes of a staged row
 constexpr int kMaxLds = 160 * 1024;
 constexpr int kMaxSplit = 8;
-constexpr int kGridX = 1 << 20;          // workgroups in a row of the grid
+constexpr int kGridX = 1 << 20;          // workgroups in a full row of the grid
 
 __device__ __forceinline__ f32x4_t mfma(uint4 a, uint4 b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a),
@@ -149,7 +149,7 @@ template <int BM, int BN>
 __device__ __forceinline__ bool pick_tile(const GemmArgs& g, Tile& t) {
   const int mb = (g.m + BM - 1) / BM, nb = g.n / BN, tiles = mb * nb * g.split;
   const int per = (tiles + kXcds - 1) / kXcds;
-  const unsigned wg = blockIdx.y * gridDim.x + blockIdx.x;  // (gridDim.x: a multiple of the XCDs)
+  const unsigned wg = blockIdx.y * kGridX + blockIdx.x;
   int i = (int)(wg % kXcds) * per + (int)(wg / kXcds);
   if (i >= tiles || (int)(wg / kXcds) >= per) return false;
   t.slice = i / (mb * nb);
