@@ -11,9 +11,10 @@
  *        projection -> cpl_swiglu -> down projection (+ residual)
  *
  * The projections are plain GEMMs: cpl_gemm (LDS-tiled MFMA) and, for
- * decode-sized batches, cpl_gemm_skinny, which streams the weights itself.  The paper does not describe the model; the layer
- * follows the published Qwen3 architecture (RMSNorm, per-head RMSNorm on
- * queries and keys before rotary embedding, SwiGLU feed-forward).
+ * decode-sized batches, cpl_gemm_skinny, which streams the weights itself.
+ * The paper does not describe the model; the layer follows the published
+ * Qwen3 architecture (RMSNorm, per-head RMSNorm on queries and keys before
+ * rotary embedding, SwiGLU feed-forward).
  *
  * Conventions: bf16 tensors are dense and row-major with 16-byte aligned
  * rows; arithmetic is fp32 (the rotation angle is formed in turns and
