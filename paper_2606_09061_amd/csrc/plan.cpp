@@ -481,8 +481,8 @@ static int64_t choose_split_steps(const cp_attn_desc& d, const Tuning& t,
 
 // The settings that depend on how a decode unit runs.  On the matrix cores the
 // kernel keeps two workgroups per CU instead of four, and a unit beside tiles
-// takes less from them.  Measured, step us of the 512-token budget mix | the
-// 2k-token prefill-heavy mix | the 64/8-head replay round | 1,700 tokens after
+// takes less from them.  Measured, step us of the 512-token budget mix | a
+// 2k-token prefill-heavy round (rows to 23 k keys) | the 64/8-head replay round | 1,700 tokens after
 // 4k and 12k keys beside 64 decode rows | 512 tokens after 20k keys beside
 // 100, at units per CU of a prefill-dominated fused step x keys per tile step:
 //   0.5 x 60   154 | 624 | 135 | 285 | 264     0.7 x 60   154 | 612 | 143 | 294 | 266
@@ -618,9 +618,9 @@ void build_plan(const cp_attn_desc& d, const cp_row_meta* rows, int32_t n_rows,
     if (fused && pf_flops > t.fuse_flops_per_byte * dec_bytes) {
       per_cu = t.fuse_units_per_cu;
       // Four q heads per kv head: where 0.5 per CU cuts rows all the same,
-      // shorter units (0.6), or the longest outlast the tiles: the 2k-token
-      // prefill-heavy mix (rows to 32 k keys, 128 tile steps a slot) 618 us on
-      // the vector units, 633 at 0.5, 605 here.  Where it leaves all rows
+      // shorter units (0.6), or the longest outlast the tiles: 4 chunks of 480
+      // tokens after up to 32 k keys beside 128 rows to 32 k 618 us on the
+      // vector units, 633 at 0.5, 605 here.  Where it leaves all rows
       // whole, whole ones stay better (1,700 tokens after 4k keys beside 64
       // rows to 8k 198 / 209), as does 0.5 with eight heads (4,056 tokens
       // beside 40 rows to 8k 133 / 138).
