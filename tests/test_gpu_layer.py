@@ -569,6 +569,8 @@ def test_gemm_of_rows_beyond_32_bits(K):
     M.gemm(a, w, out)
     torch.cuda.synchronize()
     _close(_f64(out), _f64(av) @ _f64(wv).T, abs_=1e-4)
+    del a, w
+    torch.cuda.empty_cache()
 
 
 def test_gemm_of_more_columns_than_a_grid_row_holds():
@@ -587,6 +589,8 @@ def test_gemm_of_more_columns_than_a_grid_row_holds():
     _close(_f64(out[:, rows]), _f64(a) @ _f64(wv).T, abs_=1e-4)
     out[:, rows] = 0
     assert int(torch.count_nonzero(out)) == 0
+    del w, out
+    torch.cuda.empty_cache()
 
 
 def test_gemm_rejects_unsupported_shapes():
